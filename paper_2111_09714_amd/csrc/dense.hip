@@ -17,11 +17,12 @@
 // operand layout up to the order of the contraction index (below), so weights never
 // cross lanes.
 //
-// What bounds it: per pair about 13 (C) to 25 (P, N) vector instructions and 12 to 32
-// MFMAs per 1024 pairs, nearly in balance on a SIMD.  Two waves share a SIMD; half of the
-// waves prepare the next tile (convert and stage its rows, count its pairs) before their
-// MFMA work on the present one and half after it, so that the two do not compete for the
-// same unit.  Tiles and counts are double buffered in LDS: one barrier per tile.
+// What bounds it: the vector units first (13 to 25 vector instructions per pair, of which
+// most take 4.4 clocks of a SIMD and only all-register fp32 and three-input bit operations
+// 2.5), then the MFMAs (12 to 32 of 32 clocks per 1024 pairs); two waves share a SIMD.  The
+// next tile's work (convert and stage its rows, count its pairs) is cut into slices between
+// the MFMAs of the present one, so that a wave has both kinds to issue at any time.  Tiles
+// and counts are double buffered in LDS: one barrier per tile.
 //
 // Precision: fp32 operands as fp16 (hi, lo) pairs and three products, as everywhere in
 // this library; bf16 operands, scaled by powers of two, are exact as hi alone (cosine rows,
@@ -30,6 +31,8 @@
 //   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e
 //   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan)
 //   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 #include "timing.h"
@@ -40,6 +43,7 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
 enum : int { kWeightCount = 0, kWeightStar = 1, kWeightExpect = 2 };
@@ -53,9 +57,11 @@ constexpr float kNearFloor = 1.0f / 64.0f;  // *YOSO: 1 - x^2 is raised to at le
 struct TileSide {
     const void *fx, *fa;         // fixed side: cosine (or x) rows, rows of G
     const void *sx, *sg, *sy;    // streamed side: cosine rows, rows of G, rows summed
-    const uint32_t *fpl, *spl;   // bit planes of the codes [bh][n][NW] (C, N)
+    const uint32_t *fpl, *spl;   // bit planes of the codes [bh][n][NW] (C, N; backward)
+    const uint16_t *fcodes, *scodes;  // the codes [bh][n][m] themselves (forward, which has no scratch for planes)
     void *out_p, *out_g;         // P- (C-) weighted sum of sg (forward: of sy); G-weighted sum of sy
     float *part_p, *part_g;      // split > 1: their fp32 partial sums [split][bh][n_f][64]
+    const float *max_g, *max_y;  // partial maxima of |sg|, |sy| (kMaxParts per head, heads 4 kMaxParts apart), or null: scanned
     int n_f, n_s;
 };
 
@@ -71,6 +77,115 @@ struct TileArgs {
 __device__ __forceinline__ float opaque(float x) {
     asm("" : "+s"(x));
     return x;
+}
+
+// The codes of both sides as bit planes [row][NW]: word t PW + w holds bit t of the codes
+// of hashes 32 w .. 32 w + 31 (PW = 2 for NW = 16, else 1); words past tau PW and bits past
+// m are zero.  One row per thread and word group w: the row's codes, 64 consecutive bytes,
+// are read once; 2 operations per code and bit (4 us at 2 x 131072 rows of 32 8-bit codes,
+// its traffic alone about 3).
+// Blocks past the planes' (`plane_blocks`) take partial maxima instead: block (b*4 + t)
+// kMaxParts + p writes max |x| over the p-th of kMaxParts row ranges of tensor t (0 Q, 1 dY,
+// 2 K, 3 V) of head b, from which the tiles derive their scales.
+template <int NW, bool BF16>
+__global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restrict__ qcodes,
+                                                        const uint16_t *__restrict__ kcodes,
+                                                        uint32_t *__restrict__ qpl, uint32_t *__restrict__ kpl,
+                                                        int64_t rows_q, int64_t rows_k, int m, int tau,
+                                                        int64_t plane_blocks, const void *__restrict__ q,
+                                                        const void *__restrict__ dy, const void *__restrict__ k,
+                                                        const void *__restrict__ v, int64_t n_q, int64_t n_k,
+                                                        float *__restrict__ pmax) {
+    constexpr int PW = NW == 16 ? 2 : 1, PT = NW / PW;  // planes stored per word group
+    if (blockIdx.x >= plane_blocks) {
+        const int64_t blk = blockIdx.x - plane_blocks;
+        const int p = static_cast<int>(blk % kMaxParts), t = static_cast<int>(blk / kMaxParts) & 3;
+        const int64_t b = blk / (4 * kMaxParts);
+        const void *src = t == 0 ? q : t == 1 ? dy : t == 2 ? k : v;
+        const int64_t n = t < 2 ? n_q : n_k, per = (n + kMaxParts - 1) / kMaxParts;
+        const int64_t r0 = min(n, p * per), r1 = min(n, r0 + per);
+        const int64_t base = (b * n + r0) * D, count = (r1 - r0) * D;
+        float mx = 0.f;
+        for (int64_t e0 = static_cast<int64_t>(threadIdx.x) * 8; e0 < count; e0 += 256 * 8 * 4) {
+            float x[4][8];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int64_t e = e0 + u * 256 * 8;
+                load8<BF16>(src, base + (e < count ? e : e0), x[u]);  // (past the end: this thread's first again)
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+#pragma unroll
+                for (int i = 0; i < 8; i++) mx = fmaxf(mx, fabsf(x[u][i]));
+        }
+        mx = wave_max(mx);
+        __shared__ float wred[4];
+        if ((threadIdx.x & 63) == 0) wred[threadIdx.x >> 6] = mx;
+        __syncthreads();
+        if (threadIdx.x == 0) pmax[blk] = fmaxf(fmaxf(wred[0], wred[1]), fmaxf(wred[2], wred[3]));
+        return;
+    }
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t total = (rows_q + rows_k) * PW;
+    if (t >= total) return;
+    const int64_t r = t / PW;
+    const int w = static_cast<int>(t - r * PW);
+    const bool kside = r >= rows_q;
+    const int64_t row = kside ? r - rows_q : r;
+    const uint16_t *src = (kside ? kcodes : qcodes) + row * m + 32 * w;
+    uint32_t *dst = (kside ? kpl : qpl) + row * NW + w;
+    const int valid = min(32, m - 32 * w);
+    uint32_t pl[PT];
+#pragma unroll
+    for (int j = 0; j < PT; j++) pl[j] = 0u;
+    if (valid == 32 && (m & 7) == 0) {  // (codes are 16-byte aligned)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const uint4 c4 = reinterpret_cast<const uint4 *>(src)[v];
+            const uint32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < PT; j++) {
+                    pl[j] |= __builtin_amdgcn_ubfe(c[i], j, 1) << (8 * v + 2 * i);
+                    pl[j] |= __builtin_amdgcn_ubfe(c[i], 16 + j, 1) << (8 * v + 2 * i + 1);
+                }
+        }
+    } else {
+        for (int h = 0; h < valid; h++) {
+            const uint32_t c = src[h];
+#pragma unroll
+            for (int j = 0; j < PT; j++) pl[j] |= ((c >> j) & 1u) << h;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < PT; j++) dst[j * PW] = j < tau ? pl[j] : 0u;  // (bits of a code past tau are not part of it)
+}
+
+// One plane word of a row from the codes of its word group (four groups of eight codes;
+// those past m read as zeros): bit h of the word is bit t of code h.
+__device__ __forceinline__ uint32_t plane_word(const uint4 c[4], int t) {
+    uint32_t w = 0u;
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const uint32_t x[4] = {c[v].x, c[v].y, c[v].z, c[v].w};
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            w |= __builtin_amdgcn_ubfe(x[i], t, 1) << (8 * v + 2 * i);
+            w |= __builtin_amdgcn_ubfe(x[i], 16 + t, 1) << (8 * v + 2 * i + 1);
+        }
+    }
+    return w;
+}
+// the codes of hashes 32 w .. of a row (m a multiple of 8, codes 16-byte aligned)
+__device__ __forceinline__ void load_group(uint4 c[4], const uint16_t *row, int m, int w) {
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const bool in = 32 * w + 8 * v < m;
+        c[v] = *reinterpret_cast<const uint4 *>(row + (in ? 32 * w + 8 * v : 0));
+        const uint32_t keep = in ? 0xFFFFFFFFu : 0u;
+        c[v].x &= keep; c[v].y &= keep; c[v].z &= keep; c[v].w &= keep;
+    }
 }
 
 // hi, lo of v * scale (scale a power of two, or the product rounded once in fp32)
@@ -89,6 +204,22 @@ __device__ __forceinline__ void split8_pk(const float v[8], float scale, half8 &
     }
 }
 
+// LDS by byte address.  A lane base is made opaque, so that it stays one register and the
+// constants added to it become instruction offsets.
+typedef __attribute__((address_space(3))) unsigned char *lds_bytes;
+__device__ __forceinline__ uint32_t lane_base(uint32_t a) {
+    asm("" : "+v"(a));
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ T lds_get(uint32_t a) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(a);
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(uint32_t a, const T &v) {
+    *reinterpret_cast<__attribute__((address_space(3))) T *>(a) = v;
+}
+
 // Streamed tiles: rows of 256 bytes [hi 64 | lo 64], 16-byte chunk c of row r at slot
 // c ^ f(r).  f is a bijection of r mod 16, so that 16 rows read at one chunk hit distinct
 // banks, and f >> 2 differs within every 4 aligned rows, so that a transposing read (4
@@ -97,10 +228,10 @@ __device__ __forceinline__ uint32_t tswz(int row) {
     return static_cast<uint32_t>(((row & 3) << 2) | ((row >> 2) & 3));
 }
 
-__device__ __forceinline__ half4 tile_tr(const unsigned char *p) {
+__device__ __forceinline__ half4 tile_tr(uint32_t a) {
     typedef short short4v __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) short4v lds_short4;
-    return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(p)));
+    return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4 *)(static_cast<uintptr_t>(a))));
 }
 
 __device__ __forceinline__ floatx16 mfma32(const half8 &a, const half8 &b, const floatx16 &c) {
@@ -153,31 +284,44 @@ __device__ __forceinline__ void raw_values(const Raw<BF16> &r, float v[8]) {
 }
 
 // LDS bytes of a workgroup: the double-buffered tiles and counts
-template <int WT, int SUM, int WAVES>
+template <int WT, int SUM, int NW, int WAVES>
 constexpr int tile_lds() {
     constexpr int T = 8 * WAVES;
     constexpr int tiles = 1 + (SUM != kSumP ? 1 : 0) + (WT == kWeightExpect ? 1 : 0);
-    constexpr int counts = WT == kWeightExpect ? 0 : 32 * WAVES * T * 2;
+    constexpr int counts = WT == kWeightExpect ? 0 : 32 * WAVES * T * 2 + T * NW * 4;
     return 2 * (tiles * T * 256 + counts);
 }
 
+// Waves per SIMD that the registers are cut for: two; three for the bf16 forms that need at
+// most 168 (64 x 1500 x 1030 backward: 226 -> 216 us, 192 x 1500 forward: 323 -> 283)
+template <int WT, int SUM, bool BF16, int NW>
+constexpr int kWavesPerSimd = WT == kWeightCount && SUM != kSumPG && BF16 && NW == 8 ? 3 : 2;
+
 // NW: plane words per row (8: tau <= 8; 12: tau <= 12; 16: two words per plane, tau <= 8)
 template <int WT, int SUM, bool BF16, int NW, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void tile_kernel(TileArgs args) {
+__global__ __launch_bounds__(64 * WAVES) __attribute__((
+    amdgpu_waves_per_eu(kWavesPerSimd<WT, SUM, BF16, NW>, kWavesPerSimd<WT, SUM, BF16, NW>))) void tile_kernel(TileArgs args) {
     constexpr bool kP = SUM != kSumG, kG = SUM != kSumP;
     constexpr bool kExp = WT == kWeightExpect, kStar = WT == kWeightStar;
     constexpr bool kX = WT != kWeightCount;  // a scalar product x beside G
+    constexpr bool kOwnPlanes = !kExp && !kG;  // the forward: planes built here from the codes
+    constexpr int PW = NW == 16 ? 2 : 1;       // word groups of 32 hashes
     constexpr int T = 8 * WAVES;             // streamed rows per tile
     constexpr int NB = T / 32;               // 32-row blocks per tile
     constexpr int TB = T * 256;              // LDS bytes of one tensor's tile
     constexpr int kTiles = 1 + (kG ? 1 : 0) + (kExp ? 1 : 0);
     constexpr int CROW = T * 2;              // LDS bytes of a fixed row's counts
     constexpr int CB = kExp ? 0 : 32 * WAVES * CROW;
-    constexpr int BUF = kTiles * TB + CB;
-    // tile order within a buffer: summed rows, rows of G, cosine rows, counts
-    constexpr int OY = 0, OG = TB, OX = kStar ? OY : (kG ? 2 : 1) * TB, OC = kTiles * TB;
+    constexpr int PB = kExp ? 0 : T * NW * 4;  // the streamed rows' plane words
+    // LDS: the two buffers of each kind side by side (cosine rows, rows of G, summed rows,
+    // counts, planes), so that an access class reaches all it uses from one lane base within
+    // the 16-bit offsets of the LDS instructions
+    constexpr int OX0 = 0, OG = kExp ? 2 * TB : 0, OY = OG + (kG ? 2 * TB : 0), OX = kStar ? OY : OX0;
+    constexpr int OC = OY + 2 * TB, OP = OC + 2 * CB;
+    constexpr int OSUM = kP && kG ? OG : OY;  // the first rows that sums read
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float wmax[2][WAVES];
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bytes)smem));
 
     const int64_t t0 = (args.side[0].n_f + 32 * WAVES - 1) / (32 * WAVES);
     const int64_t t1 = args.sides > 1 ? (args.side[1].n_f + 32 * WAVES - 1) / (32 * WAVES) : 0;
@@ -202,18 +346,36 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     // ---- staging role: thread t stages 8 dims (16-byte chunk) of row t / 8 of a tile
     const int srow = tid >> 3, soct = tid & 7;
     const int64_t sbase = b * ns * D + 8 * soct;
-    Raw<BF16> ry, rg, rx;
-    auto load_tile = [&](int c0) {
+    // (the tensors of a tile are loaded and staged one after another through one set of
+    // registers: part 0 the summed rows, 1 the rows of G or else the cosine rows, 2 the cosine rows)
+    Raw<BF16> raw;
+    constexpr int kParts = kTiles;
+    constexpr int kPlaneThreads = T * NW / 4;  // threads that stage 4 plane words each
+    uint4 rp;
+    uint4 rcodes[4];  // (forward: thread t builds words t % 8 and t % 8 + 8 of row t / 8 of a tile)
+    auto load_planes = [&](int c0) {
+        if constexpr (kOwnPlanes) {
+            load_group(rcodes, a.scodes + (b * ns + min(c0 + srow, ns - 1)) * args.m, args.m, soct & (PW - 1));
+        } else if constexpr (!kExp) {
+            const int e = min(tid, kPlaneThreads - 1), r = e / (NW / 4);
+            rp = reinterpret_cast<const uint4 *>(a.spl + (b * ns + min(c0 + r, ns - 1)) * NW)[e - r * (NW / 4)];
+        }
+    };
+    auto load_part = [&](int c0, int part) {
         const int64_t off = sbase + static_cast<int64_t>(min(c0 + srow, ns - 1)) * D;
-        raw_load<BF16>(ry, a.sy, off);
-        if constexpr (kG) raw_load<BF16>(rg, a.sg, off);
-        if constexpr (kExp) raw_load<BF16>(rx, a.sx, off);
+        raw_load<BF16>(raw, part == 0 ? a.sy : kG && part == 1 ? a.sg : a.sx, off);
     };
 
     // ---- the streamed tensors' largest |value| over the head (every split scans all of
     // it, so that the scales, and the results, do not depend on the share)
     float mg = 0.f, my = 0.f;
-    for (int c = srow; c < ns; c += 4 * T) {
+    const bool have_max = a.max_y != nullptr;
+    if (have_max) {
+        const int64_t e = b * 4 * kMaxParts + (lane & (kMaxParts - 1));
+        my = a.max_y[e];
+        if constexpr (kG) mg = a.max_g[e];
+    }
+    for (int c = have_max ? ns : srow; c < ns; c += 4 * T) {
         Raw<BF16> u[4], w[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -234,7 +396,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
             }
         }
     }
-    load_tile(cs0);
+    load_part(cs0, 0);
     my = wave_max(my);
     if constexpr (kG) mg = wave_max(mg);
     if (lane == 0) {
@@ -284,17 +446,41 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
         for (int s = 0; s < 4; s++) split8_pk(v[s], sc, xrh[s], xrl[s]);
     }
 
-    // ---- counting role: lane = fixed row 64 (wave mod WAVES/2) + lane, partners T/2 (wave /
-    // (WAVES/2)) + [0, T/2) of a tile, whose plane words are wave-uniform (scalar loads)
-    constexpr int HW = WAVES / 2;
-    const int crow = 64 * (wave % HW) + lane, cpart = wave / HW;
-    uint32_t qp[kExp ? 1 : NW];
-    if constexpr (!kExp) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(a.fpl + (b * nf + min(r0 + crow, nf - 1)) * NW);
+    // ---- counting role: lane = fixed rows 128 (wave mod WAVES/4) + lane and + 64 + lane,
+    // partners T/4 (wave / (WAVES/4)) + [0, T/4) of a tile
+    constexpr int QW = WAVES / 4;
+    const int crow = 128 * (wave % QW) + lane, cpart = wave / QW;
+    uint32_t qp[2][kExp ? 1 : NW];
+    if constexpr (kOwnPlanes) {
+        // the workgroup's fixed rows as planes, through the counts' space: thread t half of
+        // the words of row t / 2
+        const int row = tid >> 1, half = tid & 1;
+        uint4 c[4];
+        load_group(c, a.fcodes + (b * nf + min(r0 + row, nf - 1)) * args.m, args.m, PW == 2 ? half : 0);
 #pragma unroll
-        for (int j = 0; j < NW / 4; j++) {
-            const uint4 w4 = src[j];
-            qp[4 * j] = w4.x; qp[4 * j + 1] = w4.y; qp[4 * j + 2] = w4.z; qp[4 * j + 3] = w4.w;
+        for (int i = 0; i < NW / 2; i++) {
+            const int t = PW == 2 ? i : (NW / 2) * half + i;
+            lds_put<uint32_t>(lds0 + OC + row * (NW * 4) + 4 * (PW == 2 ? 2 * i + half : t),
+                              t < args.tau ? plane_word(c, t) : 0u);
+        }
+        __syncthreads();
+    }
+    if constexpr (!kExp) {
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const uint4 *src =
+                reinterpret_cast<const uint4 *>(a.fpl + (b * nf + min(r0 + crow + 64 * r, nf - 1)) * NW);
+#pragma unroll
+            for (int j = 0; j < NW / 4; j++) {
+                uint4 w4;
+                if constexpr (kOwnPlanes) {
+                    const u32x4 x = lds_get<u32x4>(lds0 + OC + (crow + 64 * r) * (NW * 4) + 16 * j);
+                    w4 = make_uint4(x[0], x[1], x[2], x[3]);
+                } else {
+                    w4 = src[j];
+                }
+                qp[r][4 * j] = w4.x; qp[r][4 * j + 1] = w4.y; qp[r][4 * j + 2] = w4.z; qp[r][4 * j + 3] = w4.w;
+            }
         }
     }
     // the largest count: m, or tau m times the largest weight 8/pi < 2.55
@@ -316,16 +502,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     const int eg = kG ? __builtin_amdgcn_readfirstlane(pow2_above(hg)) : 0;
     const float scy = ldexpf(1.0f, 13 - ey), scg = ldexpf(1.0f, 13 - eg);
 
-    // convert and stage the tile held in the raw registers (rows past cs1 as zeros)
-    auto stage = [&](unsigned char *buf, int c0) {
+    // convert and stage the tensor held in the raw registers (rows past cs1 as zeros)
+    const uint32_t st_h = lane_base(lds0 + srow * 256 + ((soct ^ tswz(srow)) << 4));
+    const uint32_t st_l = lane_base(lds0 + srow * 256 + (((8 + soct) ^ tswz(srow)) << 4));
+    auto stage = [&](int bi, int c0, int part) {
         const bool ok = c0 + srow < cs1;
-        unsigned char *row = buf + srow * 256;
-        const uint32_t f = tswz(srow);
-        auto put = [&](unsigned char *t, const Raw<BF16> &r, float scale, bool lo_too, bool unit) {
+        auto put = [&](uint32_t t, const Raw<BF16> &r, float scale, bool lo_too, bool unit) {
             float v[8];
             raw_values<BF16>(r, v);
-#pragma unroll
-            for (int i = 0; i < 8; i++) v[i] = ok ? v[i] : 0.f;
             if (unit) {
                 float ss = 0.f;
 #pragma unroll
@@ -334,103 +518,137 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                 scale = ss > 0.f ? kCosScale / sqrtf(ss) : 0.f;
             }
             half8 h, l;
-            split8_pk(v, scale, h, l);
-            *reinterpret_cast<half8 *>(t + ((soct ^ f) << 4)) = h;
-            if (lo_too) *reinterpret_cast<half8 *>(t + (((8 + soct) ^ f) << 4)) = l;
+            split8_pk(v, ok ? scale : 0.f, h, l);
+            lds_put<half8>(st_h + t, h);
+            if (lo_too) lds_put<half8>(st_l + t, l);
         };
-        put(row + OY, ry, scy, !BF16, false);
-        if constexpr (kG) put(row + OG, rg, scg, !BF16, false);
-        if constexpr (kExp) put(row + OX, rx, 1.0f, true, true);
+        if (part == 0) put(OY + bi * TB, raw, scy, !BF16, false);
+        else if (kG && part == 1) put(OG + bi * TB, raw, scg, !BF16, false);
+        else put(OX + bi * TB, raw, 1.0f, true, true);
     };
 
-    // counts of the tile at c0: the codes' differing hashes are OR_t (plane_t(q) ^ plane_t(k))
-    auto count = [&](unsigned char *buf, int c0) {
-        unsigned char *crow_lds = buf + OC + crow * CROW;
-        const uint32_t f = T == 64 ? (crow & 7) : ((crow >> 2) & 3);
-        const uint32_t *pl = a.spl + (b * ns + c0 + (T / 2) * cpart) * NW;
+    const uint32_t pl_w = lds0 + OP + tid * 16;
+    const uint32_t pw_w = lds0 + OP + srow * (NW * 4) + soct * 4;
+    auto stage_planes = [&](int bi) {
+        if constexpr (kOwnPlanes) {
 #pragma unroll
-        for (int s = 0; s < T / 32; s++) {  // 16 partners at a time
-            half2v c2[8];
-#pragma unroll
-            for (int p = 0; p < 16; p += 2) {
-                uint32_t u[2];
-#pragma unroll
-                for (int i = 0; i < 2; i++) {
-                    const uint32_t *w = pl + (16 * s + p + i) * NW;
-                    uint32_t d[2] = {0u, 0u}, d2[2] = {0u, 0u};
-#pragma unroll
-                    for (int j = 0; j < NW; j++) {
-                        const int z = NW == 16 ? j & 1 : 0;
-                        if constexpr (kStar) {
-                            const uint32_t x = qp[j] ^ w[j];
-                            d2[z] |= d[z] & x;  // hashes with a second differing bit
-                            d[z] |= x;
-                        } else {
-                            d[z] |= qp[j] ^ w[j];
-                        }
-                    }
-                    if constexpr (kStar) {
-                        // tau (m - differing) + (differing in one bit only)
-                        const int e = __builtin_popcount(d[0]) + (NW == 16 ? __builtin_popcount(d[1]) : 0);
-                        const int one = __builtin_popcount(d[0] & ~d2[0]) +
-                                        (NW == 16 ? __builtin_popcount(d[1] & ~d2[1]) : 0);
-                        u[i] = 0x6400u + static_cast<uint32_t>(args.tau * (args.m - e) + one);  // fp16 1024 + N
-                    } else {
-                        u[i] = 0x6400u + static_cast<uint32_t>(__builtin_popcount(d[0]) +
-                                                               (NW == 16 ? __builtin_popcount(d[1]) : 0));
-                    }
-                }
-                const half2v c = __builtin_bit_cast(half2v, u[0] | (u[1] << 16));
-                // fp16 1024 + k holds k in its low bits; both steps are exact
-                if constexpr (kStar) {
-                    c2[p / 2] = c - half2v{static_cast<_Float16>(1024.0f), static_cast<_Float16>(1024.0f)};
-                } else {
-                    const _Float16 top = static_cast<_Float16>(1024.0f + static_cast<float>(args.m));
-                    const _Float16 cs = static_cast<_Float16>(cscale);
-                    c2[p / 2] = (half2v{top, top} - c) * half2v{cs, cs};
-                }
+            for (int i = 0; i < 2; i++) {
+                const int j = soct + 8 * i, t = j / PW;
+                if (8 * i < NW && j < NW)
+                    lds_put<uint32_t>(pw_w + bi * PB + 32 * i, t < args.tau ? plane_word(rcodes, t) : 0u);
             }
-            // element e of half g holds partner 8 (e / 4) + 4 g + e % 4: pairs (2g, 2g+1), (4+2g, 5+2g)
+        } else if constexpr (!kExp) {
+            if (tid < kPlaneThreads) lds_put<u32x4>(pl_w + bi * PB, u32x4{rp.x, rp.y, rp.z, rp.w});
+        }
+    };
+
+    // Counting in slices of one partner and the lane's two fixed rows, woven between the
+    // MFMAs of the tile before.  The partner's plane words come from LDS, the same for all
+    // lanes.  (As scalar loads they cost more: a vector instruction with a scalar operand
+    // takes 4.4 clocks of a SIMD shared by two waves, the all-vector v_bitop3 2.55.)
+    // Partners in the order of the chunks that hold their counts: slice j takes partner
+    // 8 (e / 4) + 4 g + e % 4 of the group of 16, e = j % 8, g = (j / 8) % 2.
+    constexpr int NSL = T / 4;  // slices per tile
+    struct Words {
+        u32x4 w[NW / 4];
+    };
+    const uint32_t pl_r = lane_base(lds0 + OP + (T == 64 ? 16 * cpart : 16 * (cpart >> 1) + 4 * (cpart & 1)) * (NW * 4));
+    auto load_words = [&](Words &d, int bi, int j) {
+        if constexpr (!kExp) {
+            // (T / 4 is 16 or 8 partners: a whole group of 16, or its half g = cpart & 1)
+            const int e = j & 7;
+            const int r = 8 * (e >> 2) + 4 * (j >> 3) + (e & 3);
 #pragma unroll
-            for (int g = 0; g < 2; g++) {
+            for (int i = 0; i < NW / 4; i++) d.w[i] = lds_get<u32x4>(pl_r + bi * PB + r * (NW * 4) + 16 * i);
+        }
+    };
+    auto count_one = [&](const uint32_t *q, const Words &ws) -> uint32_t {
+        uint32_t d[2] = {0u, 0u}, d2[2] = {0u, 0u};
+#pragma unroll
+        for (int j = 0; j < NW; j++) {
+            const int z = NW == 16 ? j & 1 : 0;
+            const uint32_t w = ws.w[j / 4][j % 4];
+            if constexpr (kStar)  // d2: the hashes with a second differing bit
+                d2[z] = __builtin_amdgcn_bitop3_b32(d2[z], d[z], q[j] ^ w, 0xF8);
+            d[z] = __builtin_amdgcn_bitop3_b32(d[z], q[j], w, 0xF6);  // d | (q ^ k)
+        }
+        const int e = __builtin_popcount(d[0]) + (NW == 16 ? __builtin_popcount(d[1]) : 0);
+        // as an fp16 bit pattern: 1024 + k holds the integer k in its low bits
+        if constexpr (kStar) {
+            // tau (m - differing) + (differing in one bit only)
+            const int one = __builtin_popcount(d[0] & ~d2[0]) + (NW == 16 ? __builtin_popcount(d[1] & ~d2[1]) : 0);
+            return 0x6400u + static_cast<uint32_t>(args.tau * (args.m - e) + one);
+        }
+        return 0x6400u + static_cast<uint32_t>(e);
+    };
+    half2v c2[2][4];
+    uint32_t ueven[2] = {0u, 0u};
+    // (1024 + k) -> C 2^-(7 + kc) = (m - k) csc, or N = k (*YOSO), in one exact fp16 multiply-add
+    const float cm1 = kStar ? 1.0f : -cscale;
+    const half2v cmul = {static_cast<_Float16>(cm1), static_cast<_Float16>(cm1)};
+    const float ct1 = kStar ? -1024.0f : cscale * (1024.0f + static_cast<float>(args.m));
+    const half2v cadd = {static_cast<_Float16>(ct1), static_cast<_Float16>(ct1)};
+    // (rows crow and crow + 64 have one swizzle)
+    const uint32_t cw_f = T == 64 ? (crow & 7) : ((crow >> 2) & 3);
+    const uint32_t c_w0 = lane_base(lds0 + OC + crow * CROW + (((T == 64 ? 2 * cpart : cpart) ^ cw_f) << 4));
+    const uint32_t c_w1 = lane_base(lds0 + OC + crow * CROW + (((2 * cpart + 1) ^ cw_f) << 4));
+    // row r of slice j
+    auto slice = [&](int bi, int j, const Words &w, int r) {
+        if constexpr (!kExp) {
+            const uint32_t u = count_one(qp[r], w);
+            if ((j & 1) == 0) {
+                ueven[r] = u;
+                return;
+            }
+            const half2v c = __builtin_bit_cast(half2v, ueven[r] | (u << 16));
+            c2[r][(j & 7) >> 1] = __builtin_elementwise_fma(c, cmul, cadd);
+            if ((j & 7) == 7) {
                 half8 h;
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const int p = 8 * (e / 4) + 4 * g + e % 4;
-                    h[e] = c2[p / 2][p & 1];
-                }
-                const uint32_t chunk = 2 * ((T / 32) * cpart + s) + g;
-                *reinterpret_cast<half8 *>(crow_lds + ((chunk ^ f) << 4)) = h;
+                for (int e = 0; e < 8; e++) h[e] = c2[r][e >> 1][e & 1];
+                lds_put<half8>((j >> 3 ? c_w1 : c_w0) + bi * CB + 64 * r * CROW, h);
             }
         }
     };
 
     // ---- block products.  A operand of the scalar products: lane (l31, hh) = streamed row
     // 32 k + l31, dims 16 s + 8 hh + [0, 8)
-    const uint32_t fr = tswz(l31);
-    auto rows_op = [&](const unsigned char *t, int k, int s, int lo) {
-        return *reinterpret_cast<const half8 *>(t + (32 * k + l31) * 256 +
-                                                ((static_cast<uint32_t>(8 * lo + 2 * s + hh) ^ fr) << 4));
-    };
+    uint32_t ra[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+        ra[i] = lane_base(lds0 + l31 * 256 + ((static_cast<uint32_t>(2 * i + hh) ^ tswz(l31)) << 4));
+    auto rows_op = [&](int t, int k, int s, int lo) { return lds_get<half8>(ra[4 * lo + s] + t + 32 * k * 256); };
     // A operand of the sums: lane = dim 32 db + l31; element e of half hh is streamed row
     // 32 k + 16 s + 8 (e / 4) + 4 hh + e % 4, the rows whose weights register 8 s + e of the
     // lane's block result holds.  ds_read_b64_tr_b16 gives destination lane 4a+b of a 16-lane
     // group element b of the 8 bytes addressed by source lanes 4i+a (i = 0..3).
     const int l15 = lane & 15, ti = l15 >> 2, ta = l15 & 3, tg = (lane >> 4) & 1;
-    auto sum_op = [&](const unsigned char *t, int k, int s, int db, int lo) {
-        const uint32_t ch = static_cast<uint32_t>(8 * lo + 4 * db + 2 * tg + (ta >> 1));
-        const int row = 32 * k + 16 * s + 4 * hh + ti;
-        const half4 x = tile_tr(t + row * 256 + ((ch ^ tswz(4 * hh + ti)) << 4) + 8 * (ta & 1));
-        const half4 y = tile_tr(t + (row + 8) * 256 + ((ch ^ tswz(8 + 4 * hh + ti)) << 4) + 8 * (ta & 1));
+    uint32_t sa[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int row = 4 * hh + ti + 8 * h;
+            sa[i][h] = lane_base(lds0 + OSUM + row * 256 + 8 * (ta & 1) +
+                                 ((static_cast<uint32_t>(4 * i + 2 * tg + (ta >> 1)) ^ tswz(row)) << 4));
+        }
+    auto sum_op = [&](int t, int k, int s, int db, int lo) {
+        const int o = t - OSUM + (32 * k + 16 * s) * 256;
+        const half4 x = tile_tr(sa[2 * lo + db][0] + o);
+        const half4 y = tile_tr(sa[2 * lo + db][1] + o);
         return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
     };
-    // (the forward has registers to spare: its hi*lo products accumulate apart, so that the
-    // large sums are rounded once per 16 rows instead of three times)
-    floatx16 outp[2], outg[2], outl[2];
+    const int cr = 32 * wave + l31;
+    uint32_t ca_r[T / 16];
+#pragma unroll
+    for (int i = 0; i < T / 16; i++)
+        ca_r[i] = lane_base(lds0 + OC + cr * CROW +
+                            ((static_cast<uint32_t>(2 * i + hh) ^ (T == 64 ? (cr & 7) : ((cr >> 2) & 3))) << 4));
+    floatx16 outp[2], outg[2];
 #pragma unroll
     for (int db = 0; db < 2; db++)
 #pragma unroll
-        for (int i = 0; i < 16; i++) outp[db][i] = outg[db][i] = outl[db][i] = 0.f;
+        for (int i = 0; i < 16; i++) outp[db][i] = outg[db][i] = 0.f;
 
     // YOSO-E: p = (base 2^kt)^tau <= 2^15, base = 1 - arccos(c)/pi.  Two polynomials, both
     // least squares at Chebyshev nodes.  Where every |c| of a block is at most 1/2 (almost
@@ -439,17 +657,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     // relative error 2e-8.
     const int kt = kExp ? 15 / args.tau : 0;
     const float bs = ldexpf(1.0f, kt);
-    constexpr float c2 = kCosScale * kCosScale;  // a block's S is c * c2
+    constexpr float sq = kCosScale * kCosScale;  // a block's S is c * sq
     float ca[6] = {0.31830987334251404f, 0.05305203050374985f, 0.023855842649936676f,
                    0.014495517127215862f, 0.007610586937516928f, 0.013545230962336063f};
     float cq[8] = {0.45015814900398254f, 0.037513915449380875f, 0.008425663225352764f, 0.00262420903891325f,
                    0.00044531628373079f, 0.0011004807893186808f, -0.0006614952581003308f, 0.0003937508736271411f};
     {
-        float f = bs / c2;
+        float f = bs / sq;
 #pragma unroll
         for (int i = 0; i < 6; i++) {
             ca[i] *= f;
-            f /= c2 * c2;
+            f /= sq * sq;
         }
 #pragma unroll
         for (int i = 0; i < 8; i++) cq[i] *= bs;
@@ -462,34 +680,82 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
 
     const float zero = opaque(0.0f);
     auto split_w = [&](const float w[8], half8 &hi, half8 &lo) { split8_pk(w, 1.0f, hi, lo); };
-    auto dot = [&](const unsigned char *t, int k, const half8 fh[4], const half8 fl[4], bool lo) {
-        floatx16 acc;
-#pragma unroll
-        for (int i = 0; i < 16; i++) acc[i] = 0.f;
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const half8 h = rows_op(t, k, s, 0);
-            acc = mfma32(h, fh[s], acc);
-            if (lo) {
-                acc = mfma32(h, fl[s], acc);
-                acc = mfma32(rows_op(t, k, s, 1), fh[s], acc);
-            }
-        }
-        return acc;
-    };
 
-    auto compute = [&](const unsigned char *buf) {
+    // The products of a tile as a sequence of groups of one to three MFMAs on one operand
+    // pair (hi, lo) from LDS: per block 4 groups of x and 4 of G (16 dims each), then 4 of the
+    // P sum and 4 of the G sum (16 streamed rows, 32 dims each).  A group's operands are read
+    // during the group before it.
+    // hook(i, 0), hook(i, 1), i = 0 .. 8 NB - 1, are called after the first and the last MFMA
+    // of the groups that carry the next tile's work.
+    struct Op {
+        half8 h, l;
+    };
+    constexpr int kPX = kX ? 4 : 0, kPG = kG ? 4 : 0, kPP = kP ? 4 : 0;
+    constexpr int kGroups = kPX + kPG + kPP + kPG;  // per block
+    auto fetch = [&](int bi, int gi, Op &o) {
+        const int k = gi / kGroups, i = gi % kGroups;
+        if (i < kPX) {
+            o.h = rows_op(OX + bi * TB, k, i, 0);
+            if (kExp || !BF16) o.l = rows_op(OX + bi * TB, k, i, 1);
+        } else if (i < kPX + kPG) {
+            o.h = rows_op(OG + bi * TB, k, i - kPX, 0);
+            if (!BF16) o.l = rows_op(OG + bi * TB, k, i - kPX, 1);
+        } else {
+            // (db, s) of the sums; the P sum (dV from dY, or the forward) first
+            const int j = i - kPX - kPG;
+            const bool psum = j < kPP;
+            const int t = (psum && kG ? OG : OY) + bi * TB;
+            const int sd = psum ? j : j - kPP;
+            o.h = sum_op(t, k, sd & 1, sd >> 1, 0);
+            if (!BF16) o.l = sum_op(t, k, sd & 1, sd >> 1, 1);
+        }
+    };
+    auto compute = [&](int bi, auto hook) {
+        Op op[2];
+        fetch(bi, 0, op[0]);
+        // group gi of the tile: `mm(j, o)` issues its j-th MFMA; hook index hi (or -1)
+        auto group = [&](int gi, int n, int hi, auto mm) {
+            const Op &o = op[gi & 1];
+            mm(0, o);
+            __builtin_amdgcn_sched_barrier(0);
+            if (gi + 1 < kGroups * NB) fetch(bi, gi + 1, op[(gi + 1) & 1]);
+            if (hi >= 0) hook(hi, 0);
+            if (n > 1) mm(1, o);
+            __builtin_amdgcn_sched_barrier(0);
+            if (n > 2) mm(2, o);
+            if (hi >= 0) hook(hi, 1);
+        };
 #pragma unroll
         for (int k = 0; k < NB; k++) {
-            floatx16 p;
-            if constexpr (kX) p = dot(buf + OX, k, xrh, xrl, kExp || !BF16);
-            floatx16 g;
-            if constexpr (kG) g = dot(buf + OG, k, arh, arl, !BF16);
+            const int g0 = kGroups * k;
+            floatx16 p, g;
+#pragma unroll
+            for (int i = 0; i < 16; i++) p[i] = g[i] = 0.f;
+            if constexpr (kX) {
+                constexpr int n = kExp || !BF16 ? 3 : 1;
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+                    group(g0 + s, n, kG ? -1 : 8 * k + s, [&](int j, const Op &o) {
+                        p = mfma32(j == 2 ? o.l : o.h, j == 1 ? xrl[s] : xrh[s], p);
+                    });
+            }
+            half8 c16[2];
+            if constexpr (!kExp) {
+#pragma unroll
+                for (int s = 0; s < 2; s++) c16[s] = lds_get<half8>(ca_r[2 * k + s] + bi * CB);
+            }
+            if constexpr (kG) {
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+                    group(g0 + kPX + s, BF16 ? 1 : 3, 8 * k + s, [&](int j, const Op &o) {
+                        g = mfma32(j == 2 ? o.l : o.h, j == 1 ? arl[s] : arh[s], g);
+                    });
+            }
             if constexpr (kExp) {
                 float most = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; i += 2) most = fmaxf(fmaxf(most, fabsf(p[i])), fabsf(p[i + 1]));
-                if (__builtin_amdgcn_ballot_w64(most > 0.5f * c2) == 0) {
+                if (__builtin_amdgcn_ballot_w64(most > 0.5f * sq) == 0) {
 #pragma unroll
                     for (int i = 0; i < 16; i++) {
                         const float z = p[i] * p[i];
@@ -501,7 +767,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                 } else {
 #pragma unroll
                     for (int i = 0; i < 16; i++) {
-                        const float u = __saturatef(fmaf(-fabsf(p[i]), 1.0f / c2, 1.0f));
+                        const float u = __saturatef(fmaf(-fabsf(p[i]), 1.0f / sq, 1.0f));
                         float q = cq[7];
 #pragma unroll
                         for (int j = 6; j >= 0; j--) q = fmaf(q, u, cq[j]);
@@ -524,37 +790,61 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                     default: ipow16<12>(p); break;
                 }
             }
+            // The sums.  fp32 sums of a pair of halves are taken per block first (one of 32 dims
+            // at a time) and then added to the running ones: an MFMA rounds its sum every 4
+            // rows and there are three per product, and that many roundings of the large sums
+            // cost precision (dQ at 4096 rows: error 6.0e-7 summed directly).
+            // (YOSO-E's dK and dV have no registers for it; their error is P's.)
+            constexpr bool kTwoLevel = !BF16 && !(kExp && kP && kG);
+            // (hook0: the first of the hooks its four groups carry, `each` apiece, or -1)
+            auto sums = [&](int gi0, int n, int hook0, int each, floatx16 (&out)[2], bool two, const half8 (&fh)[2],
+                            const half8 (&fl)[2], bool pair) {
 #pragma unroll
-            for (int s = 0; s < 2; s++) {
-                half8 c16;
-                if constexpr (!kExp) {
-                    const int cr = 32 * wave + l31;
-                    const uint32_t f = T == 64 ? (cr & 7) : ((cr >> 2) & 3);
-                    c16 = *reinterpret_cast<const half8 *>(buf + OC + cr * CROW +
-                                                           ((static_cast<uint32_t>(4 * k + 2 * s + hh) ^ f) << 4));
+                for (int db = 0; db < 2; db++) {
+                    floatx16 t;
+                    if (two) {
+#pragma unroll
+                        for (int i = 0; i < 16; i++) t[i] = 0.f;
+                    }
+#pragma unroll
+                    for (int s = 0; s < 2; s++) {
+                        const int h = hook0 < 0 ? -1 : hook0 + each * (2 * db + s);
+                        group(gi0 + 2 * db + s, n, h, [&](int j, const Op &o) {
+                            floatx16 &acc = two ? t : out[db];
+                            if (j == 0) acc = mfma32(o.h, fh[s], acc);
+                            else if (pair && j == 1) acc = mfma32(o.h, fl[s], acc);
+                            else acc = mfma32(o.l, fh[s], acc);
+                        });
+                        if (each == 2) {
+                            hook(h + 1, 0);
+                            hook(h + 1, 1);
+                        }
+                    }
+                    if (two) out[db] += t;
                 }
-                if constexpr (kP) {
-                    // FWD sums y, the key side's backward sums g (dV from dY)
-                    const unsigned char *t = buf + (kG ? OG : OY);
-                    half8 ph, pl;
+            };
+            // P as a pair (C, exact, as hi alone); the forward, which has no G, carries the next
+            // tile's work here
+            if constexpr (kP) {
+                half8 ph[2], pl[2];
+#pragma unroll
+                for (int s = 0; s < 2; s++) {
                     if constexpr (kExp) {
                         float w[8];
 #pragma unroll
                         for (int e = 0; e < 8; e++) w[e] = p[8 * s + e];
-                        split_w(w, ph, pl);
+                        split_w(w, ph[s], pl[s]);
                     } else {
-                        ph = c16;
-                    }
-#pragma unroll
-                    for (int db = 0; db < 2; db++) {
-                        const half8 th = sum_op(t, k, s, db, 0);
-                        floatx16 &ol = kG ? outp[db] : outl[db];
-                        outp[db] = mfma32(th, ph, outp[db]);
-                        if constexpr (kExp) ol = mfma32(th, pl, ol);
-                        if constexpr (!BF16) ol = mfma32(sum_op(t, k, s, db, 1), ph, ol);
+                        ph[s] = pl[s] = c16[s];
                     }
                 }
-                if constexpr (kG) {
+                sums(g0 + kPX + kPG, 1 + (kExp ? 1 : 0) + (BF16 ? 0 : 1), kG ? -1 : kX ? 8 * k + 4 : 8 * k,
+                     kG || kX ? 1 : 2, outp, kTwoLevel && (kExp || !kG), ph, pl, kExp);
+            }
+            if constexpr (kG) {
+                half8 wh[2], wl[2];
+#pragma unroll
+                for (int s = 0; s < 2; s++) {
                     float w[8];
 #pragma unroll
                     for (int e = 0; e < 8; e++) {
@@ -564,91 +854,126 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
                         } else if constexpr (kStar) {
                             const float x = p[i] * xs;
                             const float z = fmaxf(fmaf(-x, x, 1.0f), kNearFloor);
-                            w[e] = g[i] * (static_cast<float>(c16[e]) * (__builtin_amdgcn_rsqf(z) * sw));
+                            w[e] = g[i] * (static_cast<float>(c16[s][e]) * (__builtin_amdgcn_rsqf(z) * sw));
                         } else {
-                            w[e] = fmaf(g[i], static_cast<float>(c16[e]), zero);
+                            w[e] = fmaf(g[i], static_cast<float>(c16[s][e]), zero);
                         }
                     }
-                    half8 wh, wl;
-                    split_w(w, wh, wl);
-#pragma unroll
-                    for (int db = 0; db < 2; db++) {
-                        const half8 th = sum_op(buf + OY, k, s, db, 0);
-                        outg[db] = mfma32(th, wh, outg[db]);
-                        outg[db] = mfma32(th, wl, outg[db]);
-                        if constexpr (!BF16) outg[db] = mfma32(sum_op(buf + OY, k, s, db, 1), wh, outg[db]);
-                    }
+                    split_w(w, wh[s], wl[s]);
                 }
+                sums(g0 + kPX + kPG + kPP, BF16 ? 2 : 3, 8 * k + 4, 1, outg, kTwoLevel, wh, wl, true);
             }
         }
     };
 
-    // ---- the pipeline: tile t is computed while t + 1 is staged and counted and t + 2 loaded
+    // ---- outputs
+    auto finish = [&]() {
+        auto put = [&](void *dst, float *part, const floatx16 o[2], float sc) {
+#pragma unroll
+            for (int db = 0; db < 2; db++)
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    // lane (l31, hh) holds out[row l31][32 db + 8 u + 4 hh + (0..3)] in registers 4u .. 4u+3
+                    const int64_t off = (b * nf + frow) * D + 32 * db + 8 * u + 4 * hh;
+                    const float4 x = make_float4(o[db][4 * u] * sc, o[db][4 * u + 1] * sc, o[db][4 * u + 2] * sc,
+                                           o[db][4 * u + 3] * sc);
+                    if (split > 1 || !BF16) {
+                        *reinterpret_cast<float4 *>(split > 1 ? part + sp * (args.bh * nf * D) + off
+                                                              : static_cast<float *>(dst) + off) = x;
+                    } else {
+                        uint2 w;
+                        w.x = static_cast<uint32_t>(f32_to_bf16(x.x)) | (static_cast<uint32_t>(f32_to_bf16(x.y)) << 16);
+                        w.y = static_cast<uint32_t>(f32_to_bf16(x.z)) | (static_cast<uint32_t>(f32_to_bf16(x.w)) << 16);
+                        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(dst) + off) = w;
+                    }
+                }
+        };
+        if (frow < nf) {
+            if constexpr (kP) {
+                const int e1 = kG ? eg : ey;
+                const float sc = kExp ? ldexpf(1.0f, e1 - 13 - kt * args.tau)
+                                      : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + 7 + kc);
+                put(a.out_p, a.part_p, outp, sc);
+            }
+            if constexpr (kG) {
+                const int e = (eg - 13) + (ea - kFixedExp) + (ey - 13);
+                const float half_tau = 0.5f * static_cast<float>(args.tau);
+                const float sc = kExp    ? ldexpf(half_tau, e + 7)
+                                 : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + 7 + kc + 2)
+                                         : ldexpf(half_tau / static_cast<float>(args.m), e + 7 + kc);
+                put(a.out_g, a.part_g, outg, sc);
+            }
+        }
+    };
+
+    // ---- the pipeline: while tile t is computed, t + 1 is staged and counted and t + 2 loaded
+    // (past the last tile the last one again, never used: no branch in the loop)
+    const int clast = cs0 < cs1 ? cs0 + (cs1 - 1 - cs0) / T * T : cs0;
     if (cs0 < cs1) {
-        stage(smem, cs0);
-        if constexpr (!kExp) count(smem, cs0);
-        load_tile(cs0 + T);
+        load_planes(cs0);
+#pragma unroll
+        for (int i = 0; i < kParts; i++) {
+            if (i > 0) load_part(cs0, i);
+            stage(0, cs0, i);
+        }
+        stage_planes(0);
+        load_part(min(cs0 + T, clast), 0);
+        load_planes(min(cs0 + T, clast));
+    }
+    if constexpr (!kExp) {
+        // the first tile's counts need its planes, and the second tile's planes must lie in
+        // LDS before the first step counts it
+        __syncthreads();
+        if (cs0 < cs1) {
+#pragma unroll
+            for (int j = 0; j < NSL; j++) {
+                Words w;
+                load_words(w, 0, j);
+                slice(0, j, w, 0);
+                slice(0, j, w, 1);
+            }
+            stage_planes(1);
+            load_planes(min(cs0 + 2 * T, clast));
+        }
     }
     __syncthreads();
-    const bool early = wave < HW;
-    auto step = [&](unsigned char *cur, unsigned char *nxt, int c0) {
-        const bool more = c0 + T < cs1;
-        auto ahead = [&]() {
-            stage(nxt, c0 + T);
-            load_tile(c0 + 2 * T);
-            if constexpr (!kExp) count(nxt, c0 + T);
-        };
-        if (early && more) ahead();
-        compute(cur);
-        if (!early && more) ahead();
+    // step: tile c0 is computed from `cur`; tile c0 + T is staged into `nxt` and counted (its
+    // planes lie in nxt since the step before); the planes of c0 + 2T replace those in `cur`
+    // (counted a step ago)
+    auto step = [&](int cur, int nxt, int c0) {
+        const int c1 = min(c0 + T, clast), c2n = min(c0 + 2 * T, clast), c3 = min(c0 + 3 * T, clast);
+        Words w[2];
+        load_words(w[0], nxt, 0);
+        compute(cur, [&](int i, int half) {
+            if (half == 0) {
+                if (i + 1 < NSL) load_words(w[(i + 1) & 1], nxt, i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                slice(nxt, i, w[i & 1], 0);
+            } else {
+                slice(nxt, i, w[i & 1], 1);
+                // the tile's tensors are staged in turn, each after its loads have had a third
+                // or half of a tile's time
+                constexpr int gap = 8 * NB / kParts;
+                if (i % gap == 0 && i / gap < kParts) {
+                    const int part = i / gap;
+                    stage(nxt, c1, part);
+                    load_part(part + 1 < kParts ? c1 : c2n, part + 1 < kParts ? part + 1 : 0);
+                }
+                if (i == 2) {
+                    stage_planes(cur);
+                    load_planes(c3);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
         __syncthreads();
     };
     // (two steps per turn: the buffers' addresses are constants)
     for (int c0 = cs0; c0 < cs1; c0 += 2 * T) {
-        step(smem, smem + BUF, c0);
-        if (c0 + T < cs1) step(smem + BUF, smem, c0 + T);
+        step(0, 1, c0);
+        if (c0 + T < cs1) step(1, 0, c0 + T);
     }
-
-    // ---- outputs: lane (l31, hh) holds out[row l31][32 db + 8 u + 4 hh + (0..3)] in registers 4u .. 4u+3
-    if (frow >= nf) return;
-    auto put = [&](void *dst, float *part, const floatx16 o[2], float sc) {
-#pragma unroll
-        for (int db = 0; db < 2; db++)
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int64_t off = (b * nf + frow) * D + 32 * db + 8 * u + 4 * hh;
-                const float x0 = o[db][4 * u] * sc, x1 = o[db][4 * u + 1] * sc, x2 = o[db][4 * u + 2] * sc,
-                            x3 = o[db][4 * u + 3] * sc;
-                if (split > 1) {
-                    *reinterpret_cast<float4 *>(part + sp * (args.bh * nf * D) + off) = make_float4(x0, x1, x2, x3);
-                } else if constexpr (BF16) {
-                    uint2 w;
-                    w.x = static_cast<uint32_t>(f32_to_bf16(x0)) | (static_cast<uint32_t>(f32_to_bf16(x1)) << 16);
-                    w.y = static_cast<uint32_t>(f32_to_bf16(x2)) | (static_cast<uint32_t>(f32_to_bf16(x3)) << 16);
-                    *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(dst) + off) = w;
-                } else {
-                    *reinterpret_cast<float4 *>(static_cast<float *>(dst) + off) = make_float4(x0, x1, x2, x3);
-                }
-            }
-    };
-    if constexpr (kP) {
-        const int e1 = kG ? eg : ey;
-        const float sc = kExp ? ldexpf(1.0f, e1 - 13 - kt * args.tau)
-                              : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + 7 + kc);
-        if constexpr (!kG) {
-            outp[0] += outl[0];
-            outp[1] += outl[1];
-        }
-        put(a.out_p, a.part_p, outp, sc);
-    }
-    if constexpr (kG) {
-        const int e = (eg - 13) + (ea - kFixedExp) + (ey - 13);
-        const float half_tau = 0.5f * static_cast<float>(args.tau);
-        const float sc = kExp    ? ldexpf(half_tau, e + 7)
-                         : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + 7 + kc + 2)
-                                 : ldexpf(half_tau / static_cast<float>(args.m), e + 7 + kc);
-        put(a.out_g, a.part_g, outg, sc);
-    }
+    finish();
 }
 
 __global__ void zero_rows_kernel(uint32_t *__restrict__ p, int64_t words) {
@@ -667,10 +992,62 @@ hipError_t zero_rows_async(void *p, int64_t bytes, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// dQ, dK, dV = sums over the splits of their fp32 partial outputs, in split order
+template <bool BF16>
+__global__ __launch_bounds__(256) void split_sum_kernel(SplitSum a) {
+    const int64_t total = a.count4[0] + a.count4[1] + a.count4[2];
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; t < total;
+         t += static_cast<int64_t>(gridDim.x) * 256) {
+        const int o = t < a.count4[0] ? 0 : (t < a.count4[0] + a.count4[1] ? 1 : 2);
+        const int64_t i = t - (o > 0 ? a.count4[0] : 0) - (o > 1 ? a.count4[1] : 0);
+        const int64_t n4 = o == 0 ? a.count4[0] : (o == 1 ? a.count4[1] : a.count4[2]);
+        const floatx4 *part = reinterpret_cast<const floatx4 *>(o == 0 ? a.part[0] : (o == 1 ? a.part[1] : a.part[2]));
+        void *out = o == 0 ? a.out[0] : (o == 1 ? a.out[1] : a.out[2]);
+        floatx4 acc = part[i];
+        const int split = o == 0 ? a.split[0] : (o == 1 ? a.split[1] : a.split[2]);
+        for (int sp = 1; sp < split; sp++) acc += part[sp * n4 + i];
+        if constexpr (BF16) {
+            uint2 w;
+            w.x = static_cast<uint32_t>(f32_to_bf16(acc[0])) | (static_cast<uint32_t>(f32_to_bf16(acc[1])) << 16);
+            w.y = static_cast<uint32_t>(f32_to_bf16(acc[2])) | (static_cast<uint32_t>(f32_to_bf16(acc[3])) << 16);
+            reinterpret_cast<uint2 *>(out)[i] = w;
+        } else {
+            reinterpret_cast<floatx4 *>(out)[i] = acc;
+        }
+    }
+}
+
 int64_t side_blocks(const TileArgs &a, int rows) {
     int64_t n = (a.side[0].n_f + rows - 1) / rows;
     if (a.sides > 1) n += (a.side[1].n_f + rows - 1) / rows;
     return a.bh * n;
+}
+
+// Workgroups of a launch: 8 waves (256 fixed rows, one per CU) or 4 (128 rows, two per CU),
+// the latter with the streamed rows shared among `split` workgroups where the blocks alone
+// would leave CUs idle.  Each is priced by its rounds over 256 CUs (a last round of at most
+// one 4-wave workgroup per CU at 0.62 of a full one); 4 waves stage each streamed row
+// twice as often, priced at 6%.  (64 heads of 1500 x 1030, bf16: 410 us with 8 waves, 362
+// with 4; 32 x 4096 fp32: 1123 and 1190.)
+struct TileShape {
+    bool wide;  // 8 waves
+    int split;
+    double rounds;  // rounds of a full CU's work, each over n_s / split streamed rows
+};
+constexpr int kTileMaxSplit = 16;
+constexpr int kTileMinShare = 64;  // streamed rows per share at least
+
+TileShape tile_shape(int64_t blocks8, int64_t blocks4, int64_t n_s, int max_split) {
+    if (blocks4 >= 512) {
+        const int64_t rem = blocks4 % 512;
+        const double t8 = static_cast<double>((blocks8 + 255) / 256);
+        const double t4 = 1.06 * (static_cast<double>(blocks4 / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.62 : 1.0));
+        return {t8 <= t4, 1, t8 <= t4 ? t8 : t4};
+    }
+    int split = 1;
+    while (split < max_split && blocks4 * split * 2 <= 512 && n_s >= static_cast<int64_t>(kTileMinShare) * split * 2)
+        split *= 2;
+    return {false, split, blocks4 * split <= 256 ? 0.66 : 1.06};
 }
 
 template <int WT, int SUM, bool BF16, int NW, int WAVES>
@@ -679,17 +1056,176 @@ hipError_t launch_tiles_w(const TileArgs &a, hipStream_t stream, const char *nam
     if (blocks == 0) return hipSuccess;
     KernelTimer timer(name, stream);
     hipLaunchKernelGGL((tile_kernel<WT, SUM, BF16, NW, WAVES>), dim3(static_cast<unsigned>(blocks)), dim3(64 * WAVES),
-                       (tile_lds<WT, SUM, WAVES>()), stream, a);
+                       (tile_lds<WT, SUM, NW, WAVES>()), stream, a);
     return hipGetLastError();
 }
 
 template <int WT, int SUM, bool BF16, int NW>
-hipError_t launch_tiles(const TileArgs &a, hipStream_t stream, const char *name) {
-    return side_blocks(a, 256) >= 256 ? launch_tiles_w<WT, SUM, BF16, NW, 8>(a, stream, name)
-                                      : launch_tiles_w<WT, SUM, BF16, NW, 4>(a, stream, name);
+hipError_t launch_tiles(const TileArgs &a, bool wide, hipStream_t stream, const char *name) {
+    // (more than 8 plane words leave too few registers for the 8-wave forms that also take dV
+    // or *YOSO's weight)
+    if constexpr (NW == 8 || (WT == kWeightCount && SUM == kSumG)) {
+        if (wide) return launch_tiles_w<WT, SUM, BF16, NW, 8>(a, stream, name);
+    }
+    return launch_tiles_w<WT, SUM, BF16, NW, 4>(a, stream, name);
+}
+
+// a launch without scratch: no split
+template <int WT, int SUM, bool BF16, int NW>
+hipError_t launch_tiles_alone(TileArgs &a, hipStream_t stream, const char *name) {
+    a.split = 1;
+    return launch_tiles<WT, SUM, BF16, NW>(a, tile_shape(side_blocks(a, 256), side_blocks(a, 128), 0, 1).wide, stream,
+                                           name);
 }
 
 }  // namespace
+
+hipError_t launch_split_sum(const SplitSum &a, bool bf16, hipStream_t stream) {
+    const int64_t total = a.count4[0] + a.count4[1] + a.count4[2];
+    if (total == 0) return hipSuccess;
+    const int64_t blocks = (total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096;
+    KernelTimer timer("dense_sum_kernel", stream);
+    if (bf16)
+        hipLaunchKernelGGL(split_sum_kernel<true>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL(split_sum_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+}
+
+namespace {
+
+// The shapes of the backward's launches (dK and dV; dQ; *YOSO: both in one) and their
+// partial outputs in the scratch of t.part_bytes.
+struct TilePlan {
+    TileShape kv, q;
+    size_t part_bytes;
+    bool maxima;  // taken by the prep kernel, not by a scan of each workgroup
+};
+
+TilePlan tile_plan(int64_t bh, int64_t n_q, int64_t n_k, bool star, size_t room) {
+    auto blocks = [&](int64_t n, int rows) { return bh * ((n + rows - 1) / rows); };
+    TilePlan p{};
+    for (int most = kTileMaxSplit;; most /= 2) {
+        if (star) {
+            p.kv = tile_shape(blocks(n_q, 256) + blocks(n_k, 256), blocks(n_q, 128) + blocks(n_k, 128),
+                              n_q < n_k ? n_q : n_k, most);
+            p.q = p.kv;
+        } else {
+            p.kv = tile_shape(blocks(n_k, 256), blocks(n_k, 128), n_q, most);
+            p.q = tile_shape(blocks(n_q, 256), blocks(n_q, 128), n_k, most);
+        }
+        p.part_bytes = 0;
+        if (p.q.split > 1) p.part_bytes += static_cast<size_t>(p.q.split) * bh * n_q * D * 4;
+        if (p.kv.split > 1) p.part_bytes += static_cast<size_t>(p.kv.split) * bh * n_k * D * 4 * (star ? 1 : 2);
+        if (most == 1 || p.part_bytes <= room) break;
+    }
+    // a scan costs each workgroup one more read of the streamed rows: less than the maxima's
+    // own pass while the workgroups are few rounds of short sequences
+    p.maxima = p.kv.split > 1 || p.q.split > 1 || n_q >= 2048 || n_k >= 2048;
+    return p;
+}
+
+}  // namespace
+
+double tile_rows(int64_t bh, int64_t n_q, int64_t n_k) {
+    const TilePlan p = tile_plan(bh, n_q, n_k, false, static_cast<size_t>(-1));
+    return 0.54 * p.kv.rounds * static_cast<double>(n_q) / p.kv.split +
+           0.46 * p.q.rounds * static_cast<double>(n_k) / p.q.split;
+}
+
+namespace {
+
+template <bool BF16, int NW>
+hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
+    const TilePlan plan = tile_plan(t.bh, t.n_q, t.n_k, t.star, t.part_bytes);
+    const int64_t rows_q = t.bh * t.n_q, rows_k = t.bh * t.n_k;
+    {
+        const int64_t plane_blocks = ((rows_q + rows_k) * (NW == 16 ? 2 : 1) + 255) / 256;
+        const int64_t max_blocks = plan.maxima ? t.bh * 4 * kMaxParts : 0;
+        KernelTimer timer("tile_prep_kernel", stream);
+        hipLaunchKernelGGL((tile_prep_kernel<NW, BF16>), dim3(static_cast<unsigned>(plane_blocks + max_blocks)),
+                           dim3(256), 0, stream, t.qcodes, t.kcodes, t.qpl, t.kpl, rows_q, rows_k, t.m, t.tau,
+                           plane_blocks, t.q, t.dy, t.k, t.v, t.n_q, t.n_k, t.pmax);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t nq = rows_q * D, nk = rows_k * D;
+    auto pmax = [&](int i) { return plan.maxima ? t.pmax + i * kMaxParts : nullptr; };
+    TileArgs a{};
+    a.bh = t.bh; a.m = t.m; a.tau = t.tau;
+    TileSide kv{}, q{};
+    // keys fixed (a = V), queries streamed (g = dY, y = Q)
+    kv.fa = t.v; kv.sg = t.dy; kv.sy = t.q; kv.fpl = t.kpl; kv.spl = t.qpl;
+    kv.out_p = t.dv; kv.out_g = t.dk;
+    kv.max_g = pmax(1); kv.max_y = pmax(0);
+    kv.n_f = static_cast<int>(t.n_k); kv.n_s = static_cast<int>(t.n_q);
+    // queries fixed (a = dY), keys streamed (g = V, y = K)
+    q.fa = t.dy; q.sg = t.v; q.sy = t.k; q.fpl = t.qpl; q.spl = t.kpl;
+    q.out_g = t.dq;
+    q.max_g = pmax(3); q.max_y = pmax(2);
+    q.n_f = static_cast<int>(t.n_q); q.n_s = static_cast<int>(t.n_k);
+    q.part_g = t.part;
+    kv.part_g = t.part + (plan.q.split > 1 ? plan.q.split * nq : 0);
+    kv.part_p = kv.part_g + plan.kv.split * nk;
+    if (t.star) {
+        // *YOSO: both sides the same kernel; x = q . k of the rows as given
+        kv.fx = t.k; kv.sx = t.q; kv.out_p = nullptr;
+        q.fx = t.q; q.sx = t.k;
+        a.side[0] = q; a.side[1] = kv; a.sides = 2; a.split = plan.kv.split;
+        e = launch_tiles<kWeightStar, kSumG, BF16, NW>(a, plan.kv.wide, stream, "tile_star_kernel");
+    } else {
+        a.sides = 1;
+        a.side[0] = kv; a.split = plan.kv.split;
+        e = launch_tiles<kWeightCount, kSumPG, BF16, NW>(a, plan.kv.wide, stream, "tile_kernel");
+        if (e != hipSuccess) return e;
+        a.side[0] = q; a.split = plan.q.split;
+        e = launch_tiles<kWeightCount, kSumG, BF16, NW>(a, plan.q.wide, stream, "tile_kernel");
+    }
+    if (e != hipSuccess) return e;
+    SplitSum s{};
+    s.part[0] = q.part_g; s.out[0] = t.dq; s.split[0] = plan.q.split; s.count4[0] = plan.q.split > 1 ? nq / 4 : 0;
+    s.part[1] = kv.part_g; s.out[1] = t.dk; s.split[1] = plan.kv.split; s.count4[1] = plan.kv.split > 1 ? nk / 4 : 0;
+    s.part[2] = kv.part_p; s.out[2] = t.dv; s.split[2] = plan.kv.split; s.count4[2] = t.star ? 0 : s.count4[1];
+    return launch_split_sum(s, BF16, stream);
+}
+
+}  // namespace
+
+int tile_plane_words(int m, int tau) { return m > 32 ? (tau > 8 ? 0 : 16) : (tau > 8 ? 12 : 8); }
+
+hipError_t launch_tile_backward(const TileBackward &t, bool bf16, hipStream_t stream) {
+    switch (tile_plane_words(t.m, t.tau)) {
+        case 8: return bf16 ? launch_tile_backward<true, 8>(t, stream) : launch_tile_backward<false, 8>(t, stream);
+        case 12: return bf16 ? launch_tile_backward<true, 12>(t, stream) : launch_tile_backward<false, 12>(t, stream);
+        case 16: return bf16 ? launch_tile_backward<true, 16>(t, stream) : launch_tile_backward<false, 16>(t, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+bool tile_forward_codes(const uint16_t *qcodes, const uint16_t *kcodes, int m, int tau) {
+    return tile_plane_words(m, tau) != 0 && m % 8 == 0 &&
+           ((reinterpret_cast<uintptr_t>(qcodes) | reinterpret_cast<uintptr_t>(kcodes)) & 15) == 0;
+}
+
+hipError_t launch_tile_forward(const uint16_t *qcodes, const uint16_t *kcodes, const void *v, void *y, bool bf16,
+                               int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, hipStream_t stream) {
+    TileArgs a{};
+    TileSide &s = a.side[0];
+    s.sy = v; s.fcodes = qcodes; s.scodes = kcodes; s.out_p = y;
+    s.n_f = static_cast<int>(n_q); s.n_s = static_cast<int>(n_k);
+    a.bh = bh; a.sides = 1; a.m = m; a.tau = tau;
+    auto go = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        return bf16 ? launch_tiles_alone<kWeightCount, kSumP, true, NW>(a, stream, "dense_fwd_kernel")
+                    : launch_tiles_alone<kWeightCount, kSumP, false, NW>(a, stream, "dense_fwd_kernel");
+    };
+    switch (tile_plane_words(m, tau)) {
+        case 8: return go(std::integral_constant<int, 8>{});
+        case 12: return go(std::integral_constant<int, 12>{});
+        case 16: return go(std::integral_constant<int, 16>{});
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_expect_forward(const void *q, const void *k, const void *v, void *y, bool bf16, int64_t bh,
                                  int64_t n_q, int64_t n_k, int tau, hipStream_t stream) {
@@ -699,8 +1235,8 @@ hipError_t launch_expect_forward(const void *q, const void *k, const void *v, vo
     a.side[0].fx = q; a.side[0].sx = k; a.side[0].sy = v; a.side[0].out_p = y;
     a.side[0].n_f = static_cast<int>(n_q); a.side[0].n_s = static_cast<int>(n_k);
     a.bh = bh; a.sides = 1; a.tau = tau; a.m = 1; a.split = 1;
-    return bf16 ? launch_tiles<kWeightExpect, kSumP, true, 8>(a, stream, "expect_fwd_kernel")
-                : launch_tiles<kWeightExpect, kSumP, false, 8>(a, stream, "expect_fwd_kernel");
+    return bf16 ? launch_tiles_alone<kWeightExpect, kSumP, true, 8>(a, stream, "expect_fwd_kernel")
+                : launch_tiles_alone<kWeightExpect, kSumP, false, 8>(a, stream, "expect_fwd_kernel");
 }
 
 hipError_t launch_expect_backward(const void *q, const void *k, const void *v, const void *dy, void *dq, void *dk,
@@ -720,15 +1256,15 @@ hipError_t launch_expect_backward(const void *q, const void *k, const void *v, c
     TileSide &s = a.side[0];
     s.fx = k; s.fa = v; s.sx = q; s.sg = dy; s.sy = q; s.out_p = dv; s.out_g = dk;
     s.n_f = static_cast<int>(n_k); s.n_s = static_cast<int>(n_q);
-    err = bf16 ? launch_tiles<kWeightExpect, kSumPG, true, 8>(a, stream, "expect_bwd_kv_kernel")
-               : launch_tiles<kWeightExpect, kSumPG, false, 8>(a, stream, "expect_bwd_kv_kernel");
+    err = bf16 ? launch_tiles_alone<kWeightExpect, kSumPG, true, 8>(a, stream, "expect_bwd_kv_kernel")
+               : launch_tiles_alone<kWeightExpect, kSumPG, false, 8>(a, stream, "expect_bwd_kv_kernel");
     if (err != hipSuccess) return err;
     // queries fixed, keys streamed: dQ
     s = TileSide{};
     s.fx = q; s.fa = dy; s.sx = k; s.sg = v; s.sy = k; s.out_g = dq;
     s.n_f = static_cast<int>(n_q); s.n_s = static_cast<int>(n_k);
-    return bf16 ? launch_tiles<kWeightExpect, kSumG, true, 8>(a, stream, "expect_bwd_q_kernel")
-                : launch_tiles<kWeightExpect, kSumG, false, 8>(a, stream, "expect_bwd_q_kernel");
+    return bf16 ? launch_tiles_alone<kWeightExpect, kSumG, true, 8>(a, stream, "expect_bwd_q_kernel")
+                : launch_tiles_alone<kWeightExpect, kSumG, false, 8>(a, stream, "expect_bwd_q_kernel");
 }
 
 }  // namespace yoso

@@ -21,6 +21,8 @@ struct TablePlan {
 };
 
 TablePlan plan_table(int m, int tau);
+// microseconds per row (of either side) and head of the bucket tables on a full card
+double table_row_cost(int m, int tau);
 size_t table_workspace_bytes(bool bf16, int64_t bh, int64_t n_dst, int m, int tau);
 size_t hash_lds_bytes(int m, int tau);
 
@@ -57,6 +59,43 @@ hipError_t launch_expect_forward(const void *q, const void *k, const void *v, vo
 hipError_t launch_expect_backward(const void *q, const void *k, const void *v, const void *dy, void *dq, void *dk,
                                   void *dv, bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int tau,
                                   hipStream_t stream);
+
+constexpr int kMaxParts = 8;  // partial maxima per (head, tensor)
+
+// fp32 partial outputs [split][count4 groups of four], summed in split order
+struct SplitSum {
+    const float *part[3];
+    void *out[3];
+    int64_t count4[3];
+    int split[3];
+};
+hipError_t launch_split_sum(const SplitSum &a, bool bf16, hipStream_t stream);
+
+// The backward over every (query, key) pair in dense tiles (dense.hip): dQ, dK, dV of
+// yoso_backward, or dQ, dK of *YOSO (`star`).
+struct TileBackward {
+    const uint16_t *qcodes, *kcodes;
+    const void *q, *k, *v, *dy;
+    void *dq, *dk, *dv;
+    int64_t bh, n_q, n_k;
+    int m, tau;
+    bool star;
+    uint32_t *qpl, *kpl;  // scratch: bit planes [bh][n][tile_plane_words]
+    float *pmax;          // scratch: partial maxima [bh][4][kMaxParts] of |Q|, |dY|, |K|, |V|
+    float *part;          // scratch: fp32 partial outputs of launches that split the streamed rows
+    size_t part_bytes;
+};
+int tile_plane_words(int m, int tau);  // 0: these codes have no plane layout
+hipError_t launch_tile_backward(const TileBackward &t, bool bf16, hipStream_t stream);
+// Streamed rows that a CU visits one after another in yoso_backward's launches of the tiles
+// (dK and dV 0.54 of the time, dQ 0.46): their time up to a factor.
+double tile_rows(int64_t bh, int64_t n_q, int64_t n_k);
+
+// The forward over every pair in dense tiles: codes it can take, and the launch (n_k > 0).
+bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau);
+bool tile_forward_codes(const uint16_t *qcodes, const uint16_t *kcodes, int m, int tau);
+hipError_t launch_tile_forward(const uint16_t *qcodes, const uint16_t *kcodes, const void *v, void *y, bool bf16,
+                               int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, hipStream_t stream);
 
 // T of the backward's rule: a bucket takes the table form when b_q b_k > T (b_q + b_k).
 int backward_table_threshold();

@@ -96,7 +96,6 @@ constexpr int kTileBytes = 16 * 512;   // LDS bytes of one wave's operand tile
 constexpr int kPlanTiles = 256;        // row tiles planned per run (multiple of kPassThreads)
 constexpr int kExpLds = 16384;         // rows whose exponents a pass block stages in LDS
 constexpr int kEntPad = 16;            // at least this many sentinel entries after each unit's sorted entries
-constexpr int kMaxParts = 8;           // partial maxima per (head, tensor)
 constexpr int kMantBytes = 16 * 128;   // LDS bytes of a finished tile's 16-bit mantissas (the low bytes follow)
 
 // Entries per unit: n rounded up to a multiple of 4 (16-byte aligned units), then
@@ -1874,29 +1873,6 @@ __global__ __launch_bounds__(256, TILE == 32 ? 3 : 2) void dense_kernel(DenseArg
     }
 }
 
-// dQ, dK, dV = sums over the splits of their fp32 partial outputs, in split order
-// (four values per thread, the three outputs one after another), stored as fp32 or bf16.
-struct DenseSum {
-    const float *part[3];
-    void *out[3];
-    int64_t count4[3];  // four-value groups per output (a split's partials are count4 groups apart)
-    int split;
-};
-
-template <bool BF16>
-__global__ __launch_bounds__(256) void dense_sum_kernel(DenseSum a) {
-    const int64_t total = a.count4[0] + a.count4[1] + a.count4[2];
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; t < total;
-         t += static_cast<int64_t>(gridDim.x) * 256) {
-        const int o = t < a.count4[0] ? 0 : (t < a.count4[0] + a.count4[1] ? 1 : 2);
-        const int64_t i = t - (o > 0 ? a.count4[0] : 0) - (o > 1 ? a.count4[1] : 0);
-        const float *part = o == 0 ? a.part[0] : (o == 1 ? a.part[1] : a.part[2]);
-        floatx4 acc = reinterpret_cast<const floatx4 *>(part)[i];
-        for (int sp = 1; sp < a.split; sp++) acc += reinterpret_cast<const floatx4 *>(part)[sp * a.count4[o] + i];
-        dense_store<BF16>(o == 0 ? a.out[0] : (o == 1 ? a.out[1] : a.out[2]), 4 * i, acc, 1.0f);
-    }
-}
-
 // ---------------------------------------------------------------- dense forward (short sequences)
 // Y = (1/m) sum_h B_h V (Sec. 3.1, 3.2) with the hashes summed first: Y = (1/m) C V,
 // C_ij the number of hashes under which q_i and k_j collide, every (query, key)
@@ -2277,6 +2253,65 @@ namespace {
 // *YOSO always takes the pair passes.
 bool dense_form(int64_t n_q, int64_t n_k, bool star) { return !star && n_q <= kDenseMaxN && n_k <= kDenseMaxN; }
 
+// The dense tiles (dense.hip) visit every (query, key) pair; the pair and table forms
+// visit the colliding ones but pay for a partial row per row and hash.  Both are priced in
+// microseconds, fitted to 1 to 64 heads of 1100 to 8000 rows (fp32, 32 heads, m = 32, tau =
+// 8: 2048 rows 627 us in pairs against 268 in tiles, 4096: 1413 / 978, 6000: 2343 / 2099; m =
+// 8, 2048 rows: 342 / 259, 4096: 799 / 967; 64 x 1100, m = 4: 203 / 268; bf16 32 x 4096: 932 /
+// 678; 1 x 2048: 127 / 44):
+//   tiles  per streamed row and round of workgroups, by plane words and storage;
+//   pairs  per row (both sides) a fixed share and one per hash, and per colliding pair of
+//          uniform codes.
+// Short sequences (both sides at most kDenseMaxN rows) have the 16 x 16 dense form instead of
+// the pairs: the tiles are faster from 2^19 pairs on (1 x 1024: 43 against 34 us, 12 x 512: 48
+// / 43, 384 x 512: 497 / 286); below, the launch that the other form saves is worth more (12 x
+// 128: 22 / 25 us).
+bool tile_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool bf16) {
+    const int nw = tile_plane_words(m, tau);
+    if (nw == 0 || n_q == 0 || n_k == 0 || bh == 0) return false;
+    const double pairs = static_cast<double>(n_q) * n_k, heads = static_cast<double>(bh);
+    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN) return heads * pairs >= 524288.0;
+    // (a few rows against a long side: most rows have a single partner, whose scalar product
+    // decides the row's precision; the pairs' two chains of 32 dims round it less often)
+    if (n_q < 64 || n_k < 64) return false;
+    const double words = nw == 8 ? 1.0 : nw == 12 ? 1.18 : 1.62;
+    const double tiles = (bf16 ? 0.083 : 0.119) * words * tile_rows(bh, n_q, n_k) + 25.0;
+    const double rows = static_cast<double>(n_q + n_k);
+    const double colliding = (bf16 ? 5.3e-4 : 1.0e-3) * rows + (bf16 ? 8.5e-5 : 9.7e-5) * m * rows +
+                             (bf16 ? 1.0e-6 : 5.4e-6) * m * pairs / static_cast<double>(1 << tau);
+    return tiles <= heads * colliding + 50.0;
+}
+
+// *YOSO on the tiles: one visit of a pair takes all its hashes, against partial rows and
+// pairs of m tau derived hashes (fp32, 16 x 2000, m = 32, tau = 8: 3606 against 270 us; 4
+// heads of 16384 rows, m = 4, tau = 12: 1950 against 4700, on the pairs' side of the line).
+bool tile_star_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
+    const int nw = tile_plane_words(m, tau);
+    if (nw == 0 || n_q == 0 || n_k == 0 || bh == 0) return false;
+    const double pairs = static_cast<double>(n_q) * n_k, derived = static_cast<double>(m) * tau;
+    const double tiles = (nw == 8 ? 3.3e-6 : nw == 12 ? 4.5e-6 : 6.0e-6) * pairs;
+    return tiles <= derived * (2.0e-4 * static_cast<double>(n_q + n_k) +
+                               2.8e-6 * pairs / static_cast<double>(1 << (tau - 1)));
+}
+
+// The dense tiles of dense.hip on this layout's scratch: the planes (at most 64 bytes per
+// row) take the space of the fp16 copies (256 bytes), partial outputs that of the partial rows.
+hipError_t launch_tiles_on(const uint16_t *qcodes, const uint16_t *kcodes, const void *q, const void *k, const void *v,
+                           const void *dy, bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool star,
+                           void *dq, void *dk, void *dv, const BackwardLayout &L, unsigned char *ws,
+                           hipStream_t stream) {
+    TileBackward t{};
+    t.qcodes = qcodes; t.kcodes = kcodes; t.q = q; t.k = k; t.v = v; t.dy = dy;
+    t.dq = dq; t.dk = dk; t.dv = dv;
+    t.bh = bh; t.n_q = n_q; t.n_k = n_k; t.m = m; t.tau = tau; t.star = star;
+    t.qpl = reinterpret_cast<uint32_t *>(ws + L.qs);
+    t.kpl = reinterpret_cast<uint32_t *>(ws + L.ks);
+    t.pmax = reinterpret_cast<float *>(ws + L.pmax);
+    t.part = reinterpret_cast<float *>(ws + L.pq);
+    t.part_bytes = L.pmax - L.pq;
+    return launch_tile_backward(t, bf16, stream);
+}
+
 // dQ and dK from codes with m hashes of tau bits: bucket sort, per-head maxima,
 // the fp16 split, the pair passes (weights of *YOSO when `star`) and the hash sums;
 // for short sequences the dense form instead, which also writes dV.  `L` is
@@ -2295,6 +2330,8 @@ hipError_t launch_pairs(const uint16_t *qcodes, const uint16_t *kcodes, const vo
         return zero_output(dk, bh * n_k * D * ebytes, stream);
     }
 
+    if (!star && tile_form(bh, n_q, n_k, m, tau, bf16))
+        return launch_tiles_on(qcodes, kcodes, q, k, v, dy, bf16, bh, n_q, n_k, m, tau, false, dq, dk, dv, L, ws, stream);
     {
         // Sort modes, by what fits in a workgroup's LDS: (1) the column's codes (read
         // once, with stride m) and its sorted entries staged, 6 bytes per row; (2) the
@@ -2391,19 +2428,12 @@ hipError_t launch_pairs(const uint16_t *qcodes, const uint16_t *kcodes, const vo
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
         if (split == 1) return hipSuccess;
-        KernelTimer timer("dense_sum_kernel", stream);
-        DenseSum sa;
+        SplitSum sa{};
         sa.part[0] = d.side[0].pout; sa.part[1] = d.side[1].pout; sa.part[2] = d.side[1].pout2;
         sa.out[0] = dq; sa.out[1] = dk; sa.out[2] = dv;
         sa.count4[0] = bh * n_q * D / 4; sa.count4[1] = sa.count4[2] = bh * n_k * D / 4;
-        sa.split = split;
-        const int64_t total = sa.count4[0] + 2 * sa.count4[1];
-        const int64_t grid = (total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096;
-        if (bf16)
-            hipLaunchKernelGGL(dense_sum_kernel<true>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, stream, sa);
-        else
-            hipLaunchKernelGGL(dense_sum_kernel<false>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, stream, sa);
-        return hipGetLastError();
+        sa.split[0] = sa.split[1] = sa.split[2] = split;
+        return launch_split_sum(sa, bf16, stream);
     }
 
     _Float16 *qs = reinterpret_cast<_Float16 *>(ws + L.qs), *ks = reinterpret_cast<_Float16 *>(ws + L.ks);
@@ -2473,6 +2503,25 @@ bool dense_forward_applies(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau)
     return n_q * n_k <= (int64_t{1} << 19) * (per > 1 ? per : 1);
 }
 
+// The forward's dense tiles (dense.hip) cost per pair, the tables per row, feature slice and
+// pass of hashes (several times as much in their general form, few hashes or wide slices).
+// Measured (tables or the 16 x 16 form against tiles, us): 384 x 512, m = 32, tau = 8: 168 / 105;
+// 192 x 1000: 193 / 163, bf16 197 / 142; 192 x 2000 bf16: 302 / 483; m = 64, 192 x 1000: 651 /
+// 273; m = 16, tau = 7, 64 x 1500 x 1030 bf16: 141 / 88; tau = 10, 32 x 1500: 199 / 116; m = 16, tau =
+// 8, 192 x 1000: 114 / 164; few heads: 1 x 2048: 18 / 74.  Below 768 workgroups of 128 queries the
+// tables keep what is not at least twice as dear on them.
+bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
+    const int nw = tile_plane_words(m, tau);
+    const int64_t blocks = bh * ((n_q + 127) / 128);
+    if (nw == 0 || n_k == 0 || blocks < 256) return false;
+    if (dense_forward_applies(bh, n_q, n_k, m, tau)) return true;  // (against the 16 x 16 form)
+    const double heads = static_cast<double>(bh);
+    const double tiles = heads * (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.3 : 1.6) *
+                         static_cast<double>(n_q) * n_k;
+    const double tables = heads * static_cast<double>(n_q + n_k) * table_row_cost(m, tau);
+    return tiles * (blocks >= 768 ? 1.0 : 2.0) <= tables;
+}
+
 hipError_t launch_dense_forward(const uint16_t *qcodes, const uint16_t *kcodes, const void *v, void *y, bool bf16,
                                 int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, hipStream_t stream) {
     const int64_t blocks = bh * ((n_q + kDenseRows - 1) / kDenseRows);
@@ -2493,7 +2542,7 @@ hipError_t launch_backward(const uint16_t *qcodes, const uint16_t *kcodes, const
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     // dV: the forward's table machinery with the roles of queries and keys swapped
     // (the dense form of short sequences computes it with dQ, dK)
-    const bool dense = dense_form(n_q, n_k, false) && bh > 0 && n_q > 0 && n_k > 0;
+    const bool dense = (dense_form(n_q, n_k, false) || tile_form(bh, n_q, n_k, m, tau, bf16)) && bh > 0 && n_q > 0 && n_k > 0;
     if (!dense) {
         const hipError_t e = launch_table(qcodes, dy, kcodes, dv, bf16, bh, n_q, n_k, m, tau, ws + L.table, stream);
         if (e != hipSuccess) return e;
@@ -2521,6 +2570,9 @@ hipError_t launch_backward_star(const uint16_t *qcodes, const uint16_t *kcodes, 
     // dV: eq. (gradient-v), as in launch_backward
     hipError_t e = launch_table(qcodes, dy, kcodes, dv, bf16, bh, n_q, n_k, m, tau, ws + S.table, stream);
     if (e != hipSuccess) return e;
+    if (tile_star_form(bh, n_q, n_k, m, tau))
+        return launch_tiles_on(qcodes, kcodes, q, k, v, dy, bf16, bh, n_q, n_k, m, tau, true, dq, dk, nullptr, S.pairs, ws,
+                               stream);
     uint16_t *qd = reinterpret_cast<uint16_t *>(ws + S.qcodes), *kd = reinterpret_cast<uint16_t *>(ws + S.kcodes);
     for (int side = 0; side < 2; side++) {
         const int64_t rows = bh * (side ? n_k : n_q);

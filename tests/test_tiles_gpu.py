@@ -1,0 +1,152 @@
+"""The dense tiles (csrc/dense.hip) against the fp64 oracle, at the sizes where they can
+go wrong: edges of the 32-row blocks, of the 32- and 64-row tiles and of the 128- and
+256-row workgroups, one to 64 hashes, one to twelve bits (the three plane layouts),
+streamed rows split among workgroups, and the shapes beside them that keep the pair and
+table forms.  The library's kernel timer says which form ran.  Bars as in parity.py."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from parity import TOL, check_all
+from workloads import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2111_09714_amd as Y  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    Y.lib()
+
+
+def to_dev(a, dtype):
+    t = torch.from_numpy(np.ascontiguousarray(a, np.float32))
+    return t.to(device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
+
+
+def codes_np(t):
+    return np.ascontiguousarray(t.cpu().numpy().view(np.uint16).transpose(0, 2, 1))
+
+
+def host(t):
+    return t.float().cpu().numpy().astype(np.float64)
+
+
+def inputs(bh, nq, nk, m, tau, dtype, dist="gauss"):
+    w = workloads.Workload("tiles", 1, bh, nq, 64, tau, m, dtype, dist, 977 + nq + 3 * nk + m + 100 * tau)
+    inp = make_inputs(w, n=nq, n_k=nk)
+    q, k, v, dy = (to_dev(inp[s], dtype) for s in ("q", "k", "v", "dy"))
+    R = torch.from_numpy(inp["R"]).cuda()
+    return Y.hash_qk(q, k, R, m, tau), (q, k, v, dy)
+
+
+def timed(names, call):
+    torch.cuda.synchronize()
+    Y.yoso_timing_enable(64)
+    Y.yoso_timing_reset()
+    try:
+        out = call()
+        torch.cuda.synchronize()
+        return out, {n: Y.yoso_timing_query(n)[1] for n in names}
+    finally:
+        Y.yoso_timing_enable(0)
+
+
+FORMS = ("tile_kernel", "dense_kernel", "pass_kernel", "dense_sum_kernel")
+
+BACKWARD = [
+    # (bh, n_q, n_k, m, tau, dtype, form, split): heads 0 and bh - 1 are compared
+    (2100, 17, 33, 5, 2, "f32", "tile_kernel", False),      # one partial block; 8 waves
+    (520, 33, 31, 32, 8, "bf16", "tile_kernel", False),
+    (512, 200, 200, 32, 8, "f32", "tile_kernel", False),    # 8 waves, ragged tile and rows
+    (512, 129, 257, 31, 7, "bf16", "tile_kernel", False),
+    (260, 65, 255, 8, 8, "f32", "tile_kernel", False),      # 4 waves
+    (9, 64, 5000, 32, 8, "f32", "tile_kernel", True),       # the fewest rows beside a long side
+    (9, 5000, 65, 7, 5, "bf16", "tile_kernel", True),
+    (9, 63, 5000, 32, 8, "f32", "pass_kernel", None),       # fewer: pairs
+    (1, 1100, 1030, 32, 8, "f32", "tile_kernel", True),     # few blocks: split rows
+    (3, 1025, 577, 1, 1, "f32", "tile_kernel", False),
+    (2, 1500, 1030, 32, 12, "f32", "tile_kernel", True),    # twelve plane words
+    (150, 300, 320, 16, 9, "bf16", "tile_kernel", False),
+    (2, 1030, 1500, 33, 8, "f32", "tile_kernel", True),     # two words per plane
+    (270, 128, 130, 64, 6, "f32", "tile_kernel", False),
+    (1, 2049, 4100, 64, 8, "bf16", "tile_kernel", True),
+    (8, 256, 128, 32, 8, "f32", "dense_kernel", None),      # below the rule: the 16 x 16 form
+    (1, 1100, 1100, 34, 9, "f32", "pass_kernel", None),     # no plane layout: pairs
+    (32, 3000, 3000, 2, 10, "bf16", "pass_kernel", None),   # few hashes: pairs
+]
+
+
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,form,split", BACKWARD)
+def test_backward_tiles(bh, nq, nk, m, tau, dtype, form, split):
+    (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype)
+    out, ran = timed(FORMS, lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran[form] >= 1 and sum(ran[f] for f in FORMS[:3]) == ran[form], ran
+    if split is not None:
+        assert (ran["dense_sum_kernel"] == 1) == split, ran
+    again = Y.backward(qc, kc, q, k, v, dy, m, tau)
+    assert all(torch.equal(a, b) for a, b in zip(out, again))
+    sl = [0, bh - 1] if bh > 1 else [0]
+    ref = oracle.backward(codes_np(qc[sl]), codes_np(kc[sl]), host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]), m, tau)
+    check_all(f"tiles bh{bh} {nq}x{nk} m{m} tau{tau} {dtype}",
+              [(n, host(o[sl]), r) for n, o, r in zip(("dq", "dk", "dv"), out, ref)], TOL[dtype])
+
+
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,tiles", [
+    (1, 257, 300, 32, 8, "f32", True),
+    (300, 130, 33, 5, 3, "bf16", True),
+    (2, 1100, 600, 20, 12, "f32", True),
+    (1, 500, 1030, 60, 8, "bf16", True),
+    (1, 300, 290, 40, 12, "f32", False),     # no plane layout
+    (1, 4000, 4000, 1, 4, "f32", False),     # one hash: few derived hashes
+])
+def test_star_tiles(bh, nq, nk, m, tau, dtype, tiles):
+    (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype, "mixture")
+    out, ran = timed(("tile_star_kernel", "pass_star_kernel"),
+                     lambda: Y.backward_star(qc, kc, q, k, v, dy, m, tau))
+    assert (ran["tile_star_kernel"], ran["pass_star_kernel"]) == ((1, 0) if tiles else (0, 1)), ran
+    sl = [0, bh - 1] if bh > 1 else [0]
+    ref = oracle.backward_star(codes_np(qc[sl]), codes_np(kc[sl]), host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]),
+                               m, tau)
+    check_all(f"star tiles bh{bh} {nq}x{nk} m{m} tau{tau} {dtype}",
+              [(n, host(o[sl]), r) for n, o, r in zip(("dq", "dk", "dv"), out, ref)], TOL[dtype])
+
+
+def test_bucket_tables_beside_the_tiles():
+    """Clustered rows without a plane layout: the pair passes and the table form of the
+    large buckets still serve them."""
+    m, tau = 33, 9
+    (qc, kc), (q, k, v, dy) = inputs(2, 2200, 2100, m, tau, "f32", "mixture")
+    out, ran = timed(("bucket_kernel", "tile_kernel"), lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran["bucket_kernel"] == 1 and ran["tile_kernel"] == 0, ran
+    t = Y.yoso_backward_table_threshold()
+    large = 0
+    for h in range(m):
+        bq, bk = (torch.bincount(c[0, :, h].long() & ((1 << tau) - 1), minlength=1 << tau) for c in (qc, kc))
+        large += int(((bq * bk) > t * (bq + bk)).sum())
+    assert large > 0
+    ref = oracle.backward(codes_np(qc), codes_np(kc), host(q), host(k), host(v), host(dy), m, tau)
+    check_all("buckets beside the tiles", [(n, host(o), r) for n, o, r in zip(("dq", "dk", "dv"), out, ref)], TOL["f32"])
+
+
+@pytest.mark.parametrize("bh,nq,nk,tau,dtype", [
+    (300, 33, 65, 8, "f32"),
+    (3, 1030, 127, 12, "bf16"),
+    (2, 255, 1500, 1, "f32"),
+])
+def test_expectation_tiles(bh, nq, nk, tau, dtype):
+    """Clustered and opposite rows: both polynomials of the arccos and the switch between them."""
+    (_, _), (q, k, v, dy) = inputs(bh, nq, nk, 1, tau, dtype, "mixture")
+    k[:, ::3] *= -1.0
+    y, dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    Y.yoso_expectation_forward(q, k, v, tau, y)
+    Y.yoso_expectation_backward(q, k, v, dy, tau, dq, dk, dv)
+    sl = [0, bh - 1]
+    ey, edv, edq, edk = oracle.expectation(host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]), tau)
+    check_all(f"expectation tiles bh{bh} {nq}x{nk} tau{tau} {dtype}",
+              [("y", host(y[sl]), ey), ("dq", host(dq[sl]), edq), ("dk", host(dk[sl]), edk), ("dv", host(dv[sl]), edv)],
+              TOL[dtype])
