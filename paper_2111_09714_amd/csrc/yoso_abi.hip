@@ -216,6 +216,10 @@ yoso_status yoso_forward(const uint16_t *qcodes, const uint16_t *kcodes, const v
     YOSO_TRY(check_ptr(y, bh * n_q * d, "y"));
     const bool bf16 = dtype == YOSO_BF16;
     YOSO_TRY(check_workspace(workspace, workspace_bytes, required_workspace(YOSO_OP_FORWARD, bf16, bh, n_q, n_k, m, tau)));
+    if (yoso::tile_forward_applies(bf16, bh, n_q, n_k, m, tau) && yoso::tile_forward_codes(qcodes, kcodes, m, tau))
+        return device_status(yoso::launch_tile_forward(qcodes, kcodes, v, y, bf16, bh, n_q, n_k, m, tau,
+                                                       static_cast<hipStream_t>(stream)),
+                             "yoso_forward");
     if (yoso::dense_forward_applies(bh, n_q, n_k, m, tau))
         return device_status(yoso::launch_dense_forward(qcodes, kcodes, v, y, bf16, bh, n_q, n_k, m, tau,
                                                         static_cast<hipStream_t>(stream)),

@@ -150,3 +150,24 @@ def test_expectation_tiles(bh, nq, nk, tau, dtype):
     check_all(f"expectation tiles bh{bh} {nq}x{nk} tau{tau} {dtype}",
               [("y", host(y[sl]), ey), ("dq", host(dq[sl]), edq), ("dk", host(dk[sl]), edk), ("dv", host(dv[sl]), edv)],
               TOL[dtype])
+
+
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,kernel", [
+    (520, 65, 97, 8, 5, "f32", "tile"),        # 8 waves; a partial word of hashes
+    (300, 130, 31, 32, 8, "bf16", "tile"),
+    (260, 100, 64, 24, 12, "f32", "tile"),     # twelve plane words
+    (270, 127, 129, 40, 8, "bf16", "tile"),    # two words per plane, the second partial
+    (256, 257, 1, 64, 8, "f32", "tile"),       # one key
+    (96, 1030, 600, 32, 10, "f32", "tile"),    # past the 16 x 16 form's lengths
+    (256, 100, 64, 12, 8, "f32", "other"),     # m not a multiple of 8
+    (4, 1500, 1500, 32, 8, "f32", "other"),    # few heads: tables
+])
+def test_forward_tiles(bh, nq, nk, m, tau, dtype, kernel):
+    (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype)
+    y, ran = timed(("dense_fwd_kernel", "table_kernel"), lambda: Y.forward(qc, kc, v, m, tau, n_q=nq))
+    if kernel == "tile":
+        assert ran == {"dense_fwd_kernel": 1, "table_kernel": 0}, ran
+    assert torch.equal(y, Y.forward(qc, kc, v, m, tau, n_q=nq))
+    sl = [0, bh - 1]
+    ref = oracle.forward(codes_np(qc[sl]), codes_np(kc[sl]), host(v[sl]), m, tau)
+    check_all(f"forward tiles bh{bh} {nq}x{nk} m{m} tau{tau} {dtype}", [("y", host(y[sl]), ref)], TOL[dtype])
