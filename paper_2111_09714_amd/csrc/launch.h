@@ -21,8 +21,8 @@ struct TablePlan {
 };
 
 TablePlan plan_table(int m, int tau);
-// microseconds per row (of either side) and head of the bucket tables on a full card
-double table_row_cost(int m, int tau);
+// microseconds per head of the bucket tables on a full card, over `rows` source and output rows
+double table_head_cost(int m, int tau, double rows);
 size_t table_workspace_bytes(bool bf16, int64_t bh, int64_t n_dst, int m, int tau);
 size_t hash_lds_bytes(int m, int tau);
 

@@ -2516,22 +2516,21 @@ bool dense_forward_applies(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau)
 }
 
 // The forward's dense tiles (dense.hip) cost per pair, the tables per row, feature slice and
-// pass of hashes (several times as much in their general form, few hashes or wide slices).
-// Measured (tables or the 16 x 16 form against tiles, us): 384 x 512, m = 32, tau = 8: 168 / 105;
-// 192 x 1000: 193 / 163, bf16 197 / 142; 192 x 2000 bf16: 302 / 483; m = 64, 192 x 1000: 651 /
-// 273; m = 16, tau = 7, 64 x 1500 x 1030 bf16: 141 / 88; tau = 10, 32 x 1500: 199 / 116; m = 16, tau =
-// 8, 192 x 1000: 114 / 164; few heads: 1 x 2048: 18 / 74.  Below 768 workgroups of 128 queries the
-// tables keep what is not at least twice as dear on them.
+// pass of hashes.  Measured (tables / tiles, us): 384 x 512, m = 32, tau = 8: 292 / 100, m = 8:
+// 131 / 100, m = 32, tau = 10 bf16: 721 / 118; 192 x 1000, m = 32, tau = 8: 200 / 157, m = 16: 113 /
+// 136, m = 48: 405 / 253, tau = 9: 302 / 223; 64 x 2000, m = 32, tau = 8: 103 / 180; planes of 16 words
+// spill: 192 x 1000, m = 48, tau = 10: 687 / 733; few heads: 1 x 2048: 18 / 74.  A card that is not
+// full is worse for the tiles, whose workgroups are longer: 32 x 1000 (256 of them) 36 / 44, m =
+// 32, tau = 10: 77 / 48; 64 x 1000 (512) 69 / 56, m = 16, tau = 10: 81 / 80.
 bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
     const int nw = tile_plane_words(m, tau);
     const int64_t blocks = bh * ((n_q + 127) / 128);
     if (nw == 0 || n_k == 0 || blocks < 256) return false;
     if (dense_forward_applies(bh, n_q, n_k, m, tau)) return true;  // (against the 16 x 16 form)
-    const double heads = static_cast<double>(bh);
-    const double tiles = heads * (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.3 : 1.6) *
+    const double tiles = (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.6 : 4.8) *
                          static_cast<double>(n_q) * n_k;
-    const double tables = heads * static_cast<double>(n_q + n_k) * table_row_cost(m, tau);
-    return tiles * (blocks >= 768 ? 1.0 : 2.0) <= tables;
+    return tiles * (blocks >= 768 ? 1.0 : blocks >= 512 ? 1.3 : 1.8) <=
+           table_head_cost(m, tau, static_cast<double>(n_q + n_k));
 }
 
 hipError_t launch_dense_forward(const uint16_t *qcodes, const uint16_t *kcodes, const void *v, void *y, bool bf16,

@@ -116,9 +116,9 @@ __device__ __forceinline__ void unpack(unsigned long long w, int &lo, int &hi) {
     hi = static_cast<int>(static_cast<uint32_t>(w >> 32)) + static_cast<int>(static_cast<uint32_t>(lo) >> 31);
 }
 
-// KM: how a step broadcasts key values to the lanes: 0 -> one key per step
-// (readlane), 1 -> two keys per step (two readlanes), 2 -> more (ds_bpermute).
-template <bool BF16, int DS, int KM>
+// KEYS: keys per scatter step of the staged forms (the wave's 64 lanes are KEYS keys
+// times the key's (hash, word) combos): 1, 2 or 4; 0 -> the general form.
+template <bool BF16, int DS, int KEYS>
 __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
     constexpr int P = DS / 2;   // packed words per table row
     constexpr int S = D / DS;   // slices per head
@@ -286,10 +286,10 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
     };
 
     // lane roles
-    // hashes rounded up to a power of two: fixed by (DS, KM) for the one- and
-    // two-key step forms (the host picks them exactly for those products), so their
-    // lane roles below are compile-time constants
-    constexpr int GPC = KM == 0 ? 2 * 64 / DS : (KM == 1 ? 64 / DS : 0);
+    // hashes rounded up to a power of two: fixed by (DS, KEYS) for the staged forms
+    // (the host picks them exactly for those products), so their lane roles below are
+    // compile-time constants
+    constexpr int GPC = KEYS > 0 ? 128 / (DS * (KEYS > 0 ? KEYS : 1)) : 0;
     int GP = GPC;
     if constexpr (GPC == 0) {
         GP = 1;
@@ -334,12 +334,12 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
         // ---- scatter
         // A wave owns 64-key chunks wave, wave+8, ...  Lane = key first loads and
         // quantises the chunk's values into the wave's staging area; then each step adds
-        // one (KM 0) or two (KM 1) keys into the tables, every lane taking its (hash,
-        // word) combo.  The words of eight steps are read from the staging area while the
+        // KEYS keys into the tables, every lane taking its (hash, word) combo.  The words of eight steps are read from the staging area while the
         // previous eight steps' atomics issue; the codes a lane needs are fetched 32 steps
-        // ahead and a chunk's values one chunk ahead, so no step waits for memory.
-        if constexpr (KM < 2) {
-            constexpr int KPI_C = KM == 0 ? 1 : 2;
+        // ahead (with four keys per step 16) and a chunk's values one chunk ahead, so no step
+        // waits for memory.
+        if constexpr (KEYS > 0) {
+            constexpr int KPI_C = KEYS;
             constexpr int SPC = 64 / KPI_C;  // steps per chunk
             constexpr int NG = SPC / 8;      // groups of eight steps per chunk
             const int64_t nchunks = (a.n_src + 63) / 64;
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
             // packing at the chunk loop's back edge waits for every load in flight).  With
             // one key per step the row is the same for the whole wave: a uniform row
             // pointer and a per-lane constant offset, no per-lane address arithmetic
-            constexpr int kAhead = 32;
+            constexpr int kAhead = SPC < 32 ? SPC : 32;
             static_assert(SPC % kAhead == 0, "prefetch distance must divide the chunk");
             const uint32_t last = static_cast<uint32_t>(nsrc - 1), mm = static_cast<uint32_t>(a.m);
             const uint32_t hcol = static_cast<uint32_t>(h0) + (hok ? static_cast<uint32_t>(hh) : 0u);
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
                 asm volatile("" ::: "memory");
             }
         } else {
-            // general case (few hashes, wide slices): one step at a time, combos in NI passes
+            // general case (odd or few hashes in a pass): one step at a time, combos in NI passes
             for (int ii = 0; ii < NI; ii++) {
                 const int hh = sh[ii], pp = sp[ii];
                 const bool hok = hh < gcount;
@@ -522,15 +522,15 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
             // codes of a query group: loads from clamped (always valid) positions,
             // validity applied afterwards, so the loads stay in flight
             // (raw codes only: a per-lane select on a loaded value makes the compiler
-            // branch around the load and wait for it; validity is kept apart.  The one-
-            // and two-key forms read the aligned 32-bit pair holding the code, so that the
+            // branch around the load and wait for it; validity is kept apart.  The staged
+            // forms read the aligned 32-bit pair holding the code, so that the
             // ring of codes in flight needs no widening copy at the loop's back edge)
             const uint32_t qlast = static_cast<uint32_t>(a.n_dst - 1), mm = static_cast<uint32_t>(a.m);
             uint32_t hcol[8], csh[8];
 #pragma unroll
             for (int t = 0; t < 8; t++) {
                 hcol[t] = static_cast<uint32_t>(h0) + (hh[t] < gcount ? static_cast<uint32_t>(hh[t]) : 0u);
-                csh[t] = KM < 2 ? (hcol[t] & 1u) * 16u : 0u;
+                csh[t] = KEYS > 0 ? (hcol[t] & 1u) * 16u : 0u;
             }
             const uint16_t *qhead = a.dst_codes + dst_row0 * a.m;
             // the byte offset of the 32-bit pair holding hash t's code within a row (m even)
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
 #pragma unroll
                 for (int t = 0; t < 8; t++) {
                     if (t < HL) {
-                        if constexpr (KM < 2)
+                        if constexpr (KEYS > 0)
                             cc[t] = ld<uint32_t>(qhead, qbyte + hbyte[t]);
                         else
                             cc[t] = qhead[icl * mm + hcol[t]];
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
             const unsigned char *tabc = reinterpret_cast<const unsigned char *>(tab);
             const int64_t step = static_cast<int64_t>(kTableWaves) * QPI;
             // codes of the next kGD query groups are in flight while one is summed
-            constexpr int kGD = KM < 2 ? 4 : 2;
+            constexpr int kGD = KEYS > 0 ? 4 : 2;
             uint32_t cR[kGD][8];
             // (issued in ring order, which the first groups' waits assume)
 #pragma unroll
@@ -678,38 +678,46 @@ __global__ __launch_bounds__(kTableThreads) void table_kernel(TableArgs a) {
     }
 }
 
-template <bool BF16, int DS>
-void launch_table_km(int km, const TableArgs &a, size_t lds, hipStream_t stream) {
-    const int64_t blocks = a.bh * (D / DS);
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kTableThreads);
-    if (km == 0)
-        hipLaunchKernelGGL((table_kernel<BF16, DS, 0>), grid, block, lds, stream, a);
-    else if (km == 1)
-        hipLaunchKernelGGL((table_kernel<BF16, DS, 1>), grid, block, lds, stream, a);
-    else
-        hipLaunchKernelGGL((table_kernel<BF16, DS, 2>), grid, block, lds, stream, a);
+template <bool BF16, int DS, int KEYS>
+void launch_table_keys(const TableArgs &a, size_t lds, hipStream_t stream) {
+    const dim3 grid(static_cast<unsigned>(a.bh * (D / DS))), block(kTableThreads);
+    hipLaunchKernelGGL((table_kernel<BF16, DS, KEYS>), grid, block, lds, stream, a);
 }
 
-// Step form of a table launch: 0 -> one key per step, 1 -> two keys per step (both
-// with LDS staging of a chunk's packed words), 2 -> the general form.
-int table_step_form(const TableArgs &a, int ds) {
+// (hash, word) combos of a key: what one step of the staged forms gives lanes to
+int table_combos(int G, int ds) {
     int gp = 1;
-    while (gp < a.G) gp <<= 1;
-    const int cpk = gp * (ds / 2);
-    // the one- and two-key forms read codes as aligned 32-bit pairs
-    const bool pairs = a.m % 2 == 0 && (reinterpret_cast<uintptr_t>(a.src_codes) & 3) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.dst_codes) & 3) == 0;
-    return (ds > 8 || !pairs) ? 2 : (cpk == 64 ? 0 : (cpk == 32 ? 1 : 2));
+    while (gp < G) gp <<= 1;
+    return gp * (ds / 2);
+}
+
+// Keys per scatter step of a staged form (64, 32 or 16 combos per key, hashes in pairs, slices
+// of at most 8 dims: the staging registers), 0 -> the general form, whose steps load one code
+// per lane and wait for it (m = 16, tau = 7, 192 x 1000, forward: 396 us in the general form,
+// 106 staged; 32 x 4096: 512 and 53; m = 48, tau = 10, 8 x 16384, G = 16, four keys per step: 980
+// and 300).
+int table_keys(int m, int G, int ds) {
+    const int cpk = table_combos(G, ds);
+    return ds > 8 || m % 2 != 0 || cpk > 64 || cpk < 16 ? 0 : 64 / cpk;
 }
 
 template <bool BF16>
-hipError_t launch_table_ds(int ds, int km, const TableArgs &a, size_t lds, hipStream_t stream) {
+hipError_t launch_table_ds(int ds, int keys, const TableArgs &a, size_t lds, hipStream_t stream) {
     KernelTimer timer("table_kernel", stream);
-    switch (ds) {
-        case 2: launch_table_km<BF16, 2>(km, a, lds, stream); break;
-        case 4: launch_table_km<BF16, 4>(km, a, lds, stream); break;
-        case 8: launch_table_km<BF16, 8>(km, a, lds, stream); break;
-        case 16: launch_table_km<BF16, 16>(km, a, lds, stream); break;
+    switch (8 * ds + keys) {
+        case 8 * 2 + 1: launch_table_keys<BF16, 2, 1>(a, lds, stream); break;
+        case 8 * 2 + 2: launch_table_keys<BF16, 2, 2>(a, lds, stream); break;
+        case 8 * 2 + 4: launch_table_keys<BF16, 2, 4>(a, lds, stream); break;
+        case 8 * 2: launch_table_keys<BF16, 2, 0>(a, lds, stream); break;
+        case 8 * 4 + 1: launch_table_keys<BF16, 4, 1>(a, lds, stream); break;
+        case 8 * 4 + 2: launch_table_keys<BF16, 4, 2>(a, lds, stream); break;
+        case 8 * 4 + 4: launch_table_keys<BF16, 4, 4>(a, lds, stream); break;
+        case 8 * 4: launch_table_keys<BF16, 4, 0>(a, lds, stream); break;
+        case 8 * 8 + 1: launch_table_keys<BF16, 8, 1>(a, lds, stream); break;
+        case 8 * 8 + 2: launch_table_keys<BF16, 8, 2>(a, lds, stream); break;
+        case 8 * 8 + 4: launch_table_keys<BF16, 8, 4>(a, lds, stream); break;
+        case 8 * 8: launch_table_keys<BF16, 8, 0>(a, lds, stream); break;
+        case 8 * 16: launch_table_keys<BF16, 16, 0>(a, lds, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -723,10 +731,11 @@ TablePlan plan_table(int m, int tau) {
     if (row_bytes_per_dim * m * 2 <= kTableLdsBudget) {
         p.G = m;
         p.DS = 2;
-        // widen the slice while the tables fit and a key still needs at most two instructions
-        int gp = 1;
-        while (gp < m) gp <<= 1;
-        while (p.DS < kTableMaxDS && row_bytes_per_dim * m * (p.DS * 2) <= kTableLdsBudget && gp * p.DS <= 128)
+        // widen the slice while the tables fit and a key still needs at most two
+        // instructions, but not out of a staged form: half the slices in the general form
+        // cost more (m = 16, tau = 7, 192 x 1000: 4 slices 396 us, 8 slices 106)
+        while (p.DS < kTableMaxDS && row_bytes_per_dim * m * (p.DS * 2) <= kTableLdsBudget &&
+               table_combos(m, p.DS * 2) <= 128 && !(table_keys(m, m, p.DS) && !table_keys(m, m, p.DS * 2)))
             p.DS *= 2;
     } else {
         p.DS = 2;
@@ -738,16 +747,16 @@ TablePlan plan_table(int m, int tau) {
     return p;
 }
 
-// Per feature slice and pass of hashes about 2.9e-5 us (m = 32, tau = 8: 16 slices, 192 x 1000:
-// 193 us; m = 16: 8 slices, 114 us), in the general step form 2.4e-4 (m = 16, tau = 7: 4 slices,
-// 390 us).
-double table_row_cost(int m, int tau) {
+// Per feature slice and pass of hashes: 0.022 us for the tables themselves (zeroed, scaled) and
+// per source and output row 1.9e-5 us with one key per step, 1.4e-5 with two, 1.0e-5 with four,
+// 2.5e-4 in the general form.  Modelled / measured, us: m = 32, tau = 8, 384 x 512: 255 / 292,
+// 192 x 1000: 184 / 200, 64 x 2000: 100 / 103; m = 8, tau = 8, 192 x 1000: 77 / 85; m = 32,
+// tau = 9, 192 x 1000: 307 / 302; m = 32, tau = 10, 192 x 1000: 516 / 489.
+double table_head_cost(int m, int tau, double rows) {
     const TablePlan p = plan_table(m, tau);
-    int gp = 1;
-    while (gp < p.G) gp <<= 1;
-    const int cpk = gp * (p.DS / 2);
-    const bool general = p.DS > 8 || m % 2 != 0 || (cpk != 64 && cpk != 32);
-    return (general ? 2.4e-4 : 2.9e-5) * (D / p.DS) * p.groups;
+    const int keys = table_keys(m, p.G, p.DS);
+    const double row = keys == 1 ? 1.9e-5 : keys == 2 ? 1.4e-5 : keys == 4 ? 1.0e-5 : 2.5e-4;
+    return (0.022 + row * rows) * (D / p.DS) * p.groups;
 }
 
 size_t table_workspace_bytes(bool bf16, int64_t bh, int64_t n_dst, int m, int tau) {
@@ -763,7 +772,8 @@ hipError_t launch_table(const uint16_t *src_codes, const void *values, const uin
     TablePlan p = plan_table(m, tau);
     // a head or two: narrower slices, so that more workgroups share the work (one head
     // of 512 rows: 16 -> 32 workgroups, 15 -> 11.6 us); the hashes per pass stay
-    while (p.DS > 2 && bh * (D / p.DS) < kTableFewBlocks) {
+    while (p.DS > 2 && bh * (D / p.DS) < kTableFewBlocks &&
+           !(table_keys(m, p.G, p.DS) && !table_keys(m, p.G, p.DS / 2))) {
         p.DS /= 2;
         p.lds /= 2;
     }
@@ -782,16 +792,16 @@ hipError_t launch_table(const uint16_t *src_codes, const void *values, const uin
     // fp32 outputs of long sequences: the sum bound grows with n_src (its rounding
     // step with it), the largest bucket count does not
     a.hist = !bf16 && n_src > kTableHistRows ? 1 : 0;
-    // the one- and two-key step forms also need one private dummy word per lane
-    // (targets of lanes without a valid key) and per-wave staging of a chunk's
-    // packed words (64 keys x DS/2 words); the general form needs neither (with 128
-    // KiB of tables and 16-dim slices they would not fit beside them)
-    const int km = table_step_form(a, p.DS);
-    const size_t lds = p.lds + (km < 2 ? 64 * sizeof(unsigned long long) +
-                                             static_cast<size_t>(kTableWaves) * 64 * (p.DS / 2) *
-                                                 sizeof(unsigned long long)
-                                       : 0);
-    return bf16 ? launch_table_ds<true>(p.DS, km, a, lds, stream) : launch_table_ds<false>(p.DS, km, a, lds, stream);
+    // the staged forms read codes as aligned 32-bit pairs (the entry points take 16-byte
+    // aligned pointers), and need one private dummy word per lane (targets of lanes without a valid key) and per-wave staging of a chunk's
+    // packed words (64 keys x DS/2 words) beside the tables; the general form needs
+    // neither (with 128 KiB of tables and 16-dim slices they would not fit)
+    const int keys = table_keys(m, p.G, p.DS);
+    const size_t lds = p.lds + (keys > 0 ? 64 * sizeof(unsigned long long) +
+                                               static_cast<size_t>(kTableWaves) * 64 * (p.DS / 2) *
+                                                   sizeof(unsigned long long)
+                                         : 0);
+    return bf16 ? launch_table_ds<true>(p.DS, keys, a, lds, stream) : launch_table_ds<false>(p.DS, keys, a, lds, stream);
 }
 
 }  // namespace yoso
