@@ -684,7 +684,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // The products of a tile as a sequence of groups of one to three MFMAs on one operand
     // pair (hi, lo) from LDS: per block 4 groups of x and 4 of G (16 dims each), then 4 of the
     // P sum and 4 of the G sum (16 streamed rows, 32 dims each).  A group's operands are read
-    // during the group before it.
+    // during the group before it.  x and G add their small products first, each of which rounds
+    // the sum it finds (error of dQ at 1 x 512 1.64e-7, the large one first 1.70e-7; 1 x 64 1.42e-7
+    // and 1.59e-7; the sums over rows gain nothing: 1 x 8192 2.52e-7 small first, 2.19e-7 large).
     // hook(i, 0), hook(i, 1), i = 0 .. 8 NB - 1, are called after the first and the last MFMA
     // of the groups that carry the next tile's work.
     struct Op {
@@ -736,7 +738,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
                 for (int s = 0; s < 4; s++)
                     group(g0 + s, n, kG ? -1 : 8 * k + s, [&](int j, const Op &o) {
-                        p = mfma32(j == 2 ? o.l : o.h, j == 1 ? xrl[s] : xrh[s], p);
+                        p = mfma32(n == 3 && j == 1 ? o.l : o.h, n == 3 && j == 0 ? xrl[s] : xrh[s], p);
                     });
             }
             half8 c16[2];
@@ -748,7 +750,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
                 for (int s = 0; s < 4; s++)
                     group(g0 + kPX + s, BF16 ? 1 : 3, 8 * k + s, [&](int j, const Op &o) {
-                        g = mfma32(j == 2 ? o.l : o.h, j == 1 ? arl[s] : arh[s], g);
+                        g = mfma32(!BF16 && j == 1 ? o.l : o.h, !BF16 && j == 0 ? arl[s] : arh[s], g);
                     });
             }
             if constexpr (kExp) {
@@ -893,7 +895,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 const int e1 = kG ? eg : ey;
                 const float sc = kExp ? ldexpf(1.0f, e1 - 13 - kt * args.tau)
                                       : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + 7 + kc);
-                put(a.out_p, a.part_p, outp, sc);
+                // (the dQ side of a launch for both sides has no P output)
+                if (a.out_p != nullptr) put(a.out_p, a.part_p, outp, sc);
             }
             if constexpr (kG) {
                 const int e = (eg - 13) + (ea - kFixedExp) + (ey - 13);
@@ -1098,6 +1101,7 @@ namespace {
 // partial outputs in the scratch of t.part_bytes.
 struct TilePlan {
     TileShape kv, q;
+    bool merged;  // both sides in one launch of the form that also takes dV
     size_t part_bytes;
     bool maxima;  // taken by the prep kernel, not by a scan of each workgroup
 };
@@ -1105,8 +1109,14 @@ struct TilePlan {
 TilePlan tile_plan(int64_t bh, int64_t n_q, int64_t n_k, bool star, size_t room) {
     auto blocks = [&](int64_t n, int rows) { return bh * ((n + rows - 1) / rows); };
     TilePlan p{};
+    // A few heads (both sides together below 512 workgroups of 128 rows) take one launch for
+    // both sides, dQ's in the same form: its unused P sum is cheaper than a second launch with
+    // most CUs idle (backward, m = 32, tau = 8: 2 x 512 28.9 us in two launches, 20.6 in one; 1 x
+    // 2048 43.4 / 34.6, bf16 41.4 / 28.5; 2 x 4096 100 / 91).  Both sides have one split, bounded
+    // by the shorter: sides of unlike lengths keep two launches.
+    p.merged = !star && blocks(n_q, 128) + blocks(n_k, 128) < 512 && n_q <= 4 * n_k && n_k <= 4 * n_q;
     for (int most = kTileMaxSplit;; most /= 2) {
-        if (star) {
+        if (star || p.merged) {
             p.kv = tile_shape(blocks(n_q, 256) + blocks(n_k, 256), blocks(n_q, 128) + blocks(n_k, 128),
                               n_q < n_k ? n_q : n_k, most);
             p.q = p.kv;
@@ -1129,6 +1139,7 @@ TilePlan tile_plan(int64_t bh, int64_t n_q, int64_t n_k, bool star, size_t room)
 
 double tile_rows(int64_t bh, int64_t n_q, int64_t n_k) {
     const TilePlan p = tile_plan(bh, n_q, n_k, false, static_cast<size_t>(-1));
+    if (p.merged) return 0.54 * p.kv.rounds * static_cast<double>(n_q > n_k ? n_q : n_k) / p.kv.split;
     return 0.54 * p.kv.rounds * static_cast<double>(n_q) / p.kv.split +
            0.46 * p.q.rounds * static_cast<double>(n_k) / p.q.split;
 }
@@ -1173,6 +1184,9 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
         q.fx = t.q; q.sx = t.k;
         a.side[0] = q; a.side[1] = kv; a.sides = 2; a.split = plan.kv.split;
         e = launch_tiles<kWeightStar, kSumG, BF16, NW>(a, plan.kv.wide, stream, "tile_star_kernel");
+    } else if (plan.merged) {
+        a.side[0] = kv; a.side[1] = q; a.sides = 2; a.split = plan.kv.split;
+        e = launch_tiles<kWeightCount, kSumPG, BF16, NW>(a, plan.kv.wide, stream, "tile_kernel");
     } else {
         a.sides = 1;
         a.side[0] = kv; a.split = plan.kv.split;

@@ -49,6 +49,8 @@
 //                  dQ, dK and dV as dense masked MFMA blocks, no partial rows.
 //   dense_fwd_kernel  the forward for many heads of short sequences, Y = (1/m) C V,
 //                  C counted from bit planes of the codes.
+// These two keep the calls that the 32 x 32 tiles of dense.hip do not take: hash counts and
+// code bits without a plane layout there, and a few rows on one side.
 // gfx950's global fp32 atomics sustain roughly 1.3 TB/s of payload, so a plain
 // store of every partial plus one coalesced reduction beats accumulating with
 // atomics.  Every fp32 product uses three fp16 MFMAs (hi*hi + hi*lo + lo*hi).
@@ -2275,23 +2277,28 @@ bool dense_form(int64_t n_q, int64_t n_k, bool star) { return !star && n_q <= kD
 //   pairs  per row (both sides) a fixed share and one per hash, and per colliding pair of
 //          uniform codes.
 // Short sequences (both sides at most kDenseMaxN rows) have the 16 x 16 dense form instead of
-// the pairs: the tiles are faster from 2^19 pairs on (1 x 1024: 43 against 34 us, 12 x 512: 48
-// / 43, 384 x 512: 497 / 286); below, the launch that the other form saves is worth more (12 x
-// 128: 22 / 25 us).
+// the pairs (us, that form / tiles): 384 x 512 497 / 286, 12 x 512 48 / 32, 1 x 1024 43 / 26, 1 x 512
+// 27.5 / 19.2, 1 x 256 23.4 / 18.2, 1 x 64 17.7 / 15.5, 128 x 64 27.4 / 15.4; with fewer rows on a
+// side and few pairs both are launches only (1 x 32: 16.0 / 15.3).
 bool tile_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool bf16) {
     const int nw = tile_plane_words(m, tau);
     if (nw == 0 || n_q == 0 || n_k == 0 || bh == 0) return false;
     const double pairs = static_cast<double>(n_q) * n_k, heads = static_cast<double>(bh);
-    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN) return heads * pairs >= 524288.0;
+    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN && heads * pairs >= 524288.0) return true;
     // (a few rows against a long side: most rows have a single partner, whose scalar product
     // decides the row's precision; the pairs' two chains of 32 dims round it less often)
     if (n_q < 64 || n_k < 64) return false;
+    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN) return true;
     const double words = nw == 8 ? 1.0 : nw == 12 ? 1.18 : 1.62;
     const double tiles = (bf16 ? 0.083 : 0.119) * words * tile_rows(bh, n_q, n_k) + 25.0;
     const double rows = static_cast<double>(n_q + n_k);
-    const double colliding = (bf16 ? 5.3e-4 : 1.0e-3) * rows + (bf16 ? 8.5e-5 : 9.7e-5) * m * rows +
-                             (bf16 ? 1.0e-6 : 5.4e-6) * m * pairs / static_cast<double>(1 << tau);
-    return tiles <= heads * colliding + 50.0;
+    // (fewer than some 128 (head, hash) units leave CUs without one: 1 x 8192 540 us in pairs, 174
+    // in tiles, 4 x 8192 615 / 582.  Past 8192 rows the tables' dV rounds less than the tiles')
+    const bool idle = heads * m < 128.0 && n_q <= 8192 && n_k <= 8192;
+    const double busy = idle ? 128.0 / m : heads;
+    const double colliding = busy * ((bf16 ? 5.3e-4 : 1.0e-3) * rows + (bf16 ? 8.5e-5 : 9.7e-5) * m * rows) +
+                             heads * (bf16 ? 1.0e-6 : 5.4e-6) * m * pairs / static_cast<double>(1 << tau);
+    return tiles <= colliding + 50.0;
 }
 
 // *YOSO on the tiles: one visit of a pair takes all its hashes, against partial rows and
@@ -2518,16 +2525,16 @@ bool dense_forward_applies(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau)
 // The forward's dense tiles (dense.hip) cost per pair, the tables per row, feature slice and
 // pass of hashes.  Measured (tables / tiles, us): 384 x 512, m = 32, tau = 8: 292 / 100, m = 8:
 // 131 / 100, m = 32, tau = 10 bf16: 721 / 118; 192 x 1000, m = 32, tau = 8: 200 / 157, m = 16: 113 /
-// 136, m = 48: 405 / 253, tau = 9: 302 / 223; 64 x 2000, m = 32, tau = 8: 103 / 180; planes of 16 words
-// spill: 192 x 1000, m = 48, tau = 10: 687 / 733; few heads: 1 x 2048: 18 / 74.  A card that is not
-// full is worse for the tiles, whose workgroups are longer: 32 x 1000 (256 of them) 36 / 44, m =
-// 32, tau = 10: 77 / 48; 64 x 1000 (512) 69 / 56, m = 16, tau = 10: 81 / 80.
+// 136, m = 48: 405 / 253, tau = 9: 302 / 223; 64 x 2000, m = 32, tau = 8: 103 / 180; few
+// heads: 1 x 2048: 18 / 74.  A card that is not full is worse for the tiles, whose workgroups are
+// longer: 32 x 1000 (256 of them) 36 / 44, tau = 10: 77 / 48; 64 x 1000 (512) 69 / 56, m = 16, tau =
+// 10: 81 / 80.
 bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
     const int nw = tile_plane_words(m, tau);
     const int64_t blocks = bh * ((n_q + 127) / 128);
     if (nw == 0 || n_k == 0 || blocks < 256) return false;
     if (dense_forward_applies(bh, n_q, n_k, m, tau)) return true;  // (against the 16 x 16 form)
-    const double tiles = (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.6 : 4.8) *
+    const double tiles = (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.45 : 1.75) *
                          static_cast<double>(n_q) * n_k;
     return tiles * (blocks >= 768 ? 1.0 : blocks >= 512 ? 1.3 : 1.8) <=
            table_head_cost(m, tau, static_cast<double>(n_q + n_k));

@@ -75,7 +75,13 @@ BACKWARD = [
     (2, 1030, 1500, 33, 8, "f32", "tile_kernel", True),     # two words per plane
     (270, 128, 130, 64, 6, "f32", "tile_kernel", False),
     (1, 2049, 4100, 64, 8, "bf16", "tile_kernel", True),
-    (8, 256, 128, 32, 8, "f32", "dense_kernel", None),      # below the rule: the 16 x 16 form
+    (8, 63, 128, 32, 8, "f32", "dense_kernel", None),       # below the rule: the 16 x 16 form
+    (1, 64, 64, 32, 8, "f32", "tile_kernel", False),        # a few heads: both sides in one launch
+    (1, 512, 512, 32, 8, "f32", "tile_kernel", True),
+    (2, 1023, 65, 16, 10, "bf16", "tile_kernel", True),
+    (3, 300, 700, 32, 12, "f32", "tile_kernel", True),
+    (31, 1024, 1024, 32, 8, "f32", "tile_kernel", False),   # 496 workgroups, one launch; 32 heads: two
+    (32, 1024, 1024, 32, 8, "bf16", "tile_kernel", None),
     (1, 1100, 1100, 34, 9, "f32", "pass_kernel", None),     # no plane layout: pairs
     (32, 3000, 3000, 2, 10, "bf16", "pass_kernel", None),   # few hashes: pairs
 ]
