@@ -36,11 +36,11 @@
  *     magnitude; R is staged unscaled, so |R| must stay below 65504 (entries
  *     below about 2^-3 keep their value to 2^-24 absolute).  The backward and
  *     YOSO-E scale every operand by a power of two before it is split into
- *     fp16 (hi, lo) pairs (per head and tensor, per row, or per 64-row tile),
+ *     fp16 (hi, lo) pairs (per head and tensor, or per row),
  *     so V, dY, Q, K may have any magnitude between about 2^-40 and 2^40;
- *     values more than about 2^20 below the largest of their head (backward)
- *     or tile (YOSO-E) keep less than 22 significant bits.
- *   - Precision.  Y and dV are accumulated as exact fixed-point integers: each
+ *     values more than about 2^20 below the largest of their head
+ *     keep less than 22 significant bits.
+ *   - Precision.  Y and dV from the bucket tables are accumulated as exact fixed-point integers: each
  *     value of feature dim d is rounded to a multiple of 2^-k_d, where 2^k_d is
  *     the largest power of two keeping 2^k_d (1 + 2^-10) times a bound on every
  *     bucket sum of |value| of that dim below 2^30: the dim's sum of |value|
@@ -165,12 +165,12 @@ yoso_status yoso_fast_hash(const void *x, yoso_dtype dtype, int64_t bh, int64_t 
  * qcodes [bh][n_q][m], kcodes [bh][n_k][m]  from yoso_hash with the same R.
  * v      [bh][n_k][d],  y [bh][n_q][d]  (dtype).  Queries whose buckets are empty
  * get 0 (no renormalisation).
- * Many heads of short sequences (both sides at most 1024 rows, enough heads to
- * fill the GPU) take the same sum as y = (1/m) C v, C[i][j] the number of hashes
- * under which query i and key j collide, counted pair by pair from the codes; the
- * result differs from the tables' only in the rounding of the additions.
- * workspace: yoso_workspace_bytes(YOSO_OP_FORWARD, ...) bytes (0 for that form
- * and for every shape whose tables fit in one LDS pass; then workspace may be
+ * Enough heads of short sequences to fill the GPU take the same sum as
+ * y = (1/m) C v, C[i][j] the number of hashes under which query i and key j
+ * collide, counted pair by pair from the codes, where that is cheaper than the
+ * tables; the result differs from theirs only in the rounding of the additions.
+ * workspace: yoso_workspace_bytes(YOSO_OP_FORWARD, ...) bytes (0 for the short
+ * shapes that never take the tables and for every shape whose tables fit in one LDS pass; then workspace may be
  * NULL).
  */
 yoso_status yoso_forward(const uint16_t *qcodes, const uint16_t *kcodes, const void *v,
@@ -198,7 +198,10 @@ yoso_status yoso_forward(const uint16_t *qcodes, const uint16_t *kcodes, const v
  * yoso_backward_table_threshold() is summed in the table form of Sec. 3.3
  * restricted to that bucket (one d x d matrix per side and bucket, applied to the
  * bucket's rows); the others pair by pair.  Both give the same sums up to the
- * order of fp32 additions.
+ * order of fp32 additions.  Where every (query, key) pair is cheaper to visit than
+ * the partial rows (short sequences, and up to some thousands of rows), dq, dk and
+ * dv are dense blocks weighted by the collision counts, in the same workspace:
+ * the same sums again, added in fp32.
  */
 yoso_status yoso_backward(const uint16_t *qcodes, const uint16_t *kcodes, const void *q,
                           const void *k, const void *v, const void *dy, yoso_dtype dtype,
@@ -229,8 +232,9 @@ yoso_status yoso_backward(const uint16_t *qcodes, const uint16_t *kcodes, const 
  * workspace: yoso_workspace_bytes(YOSO_OP_BACKWARD_STAR, ...) bytes, about
  * (3*m*tau*d + 9*m*tau + 8*d) * (n_q + n_k) * bh (the pairs of m*tau derived
  * (tau-1)-bit hashes, one 24-bit partial row per row and derived hash); m*tau is
- * also the limit on bh that yoso_backward puts on m.  Its pair pass does about
- * tau + 1 times the work of yoso_backward's (pairs one bit apart count too).
+ * also the limit on bh that yoso_backward puts on m.  In pairs it does about tau + 1
+ * times the work of yoso_backward (pairs one bit apart count too); where that is
+ * cheaper, dense blocks visit every pair once for all hashes, in the same workspace.
  */
 yoso_status yoso_backward_star(const uint16_t *qcodes, const uint16_t *kcodes, const void *q, const void *k,
                                const void *v, const void *dy, yoso_dtype dtype, int64_t bh, int64_t n_q,
@@ -339,8 +343,9 @@ const char *yoso_last_error(void);
  * first launch and live until the next yoso_timing_enable call; 0 disables and
  * frees them).  yoso_timing_reset() forgets the launches recorded so far.
  * yoso_timing_query() waits for the recorded events of `kernel` ("hash_kernel",
- * "fast_hash_kernel", "fast_hyperplanes_kernel", "table_kernel", "sort_kernel", "split_kernel", "pass_kernel", "reduce_kernel",
- * "zero_kernel", "l2norm_kernel", "l2norm_bwd_kernel", "expect_fwd_kernel",
+ * "fast_hash_kernel", "fast_hyperplanes_kernel", "table_kernel", "sort_kernel", "split_kernel", "pass_kernel", "bucket_kernel",
+ * "reduce_kernel", "dense_kernel", "dense_fwd_kernel", "tile_prep_kernel", "tile_kernel",
+ * "tile_star_kernel", "pass_star_kernel", "dense_sum_kernel", "zero_kernel", "l2norm_kernel", "l2norm_bwd_kernel", "expect_fwd_kernel",
  * "expect_bwd_kv_kernel", "expect_bwd_q_kernel")
  * and returns the summed duration and the launch count.
  * Not thread-safe with respect to concurrent launches on other threads' streams
