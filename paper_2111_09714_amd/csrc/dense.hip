@@ -30,7 +30,8 @@
 //   cosine rows     unit length times 2^4
 //   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e
 //   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan)
-//   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15
+//   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15;
+//                   P itself by pbase^tau, just below 2^16 (expect_scale)
 #include <type_traits>
 
 #include "common.h"
@@ -70,6 +71,7 @@ struct TileArgs {
     int64_t bh;
     int sides, m, tau;
     int split;  // workgroups per block of fixed rows, each streaming a contiguous share
+    float pbase, pinv;  // YOSO-E: p = (base pbase)^tau, 1 / pbase^tau
 };
 
 // A constant the compiler does not see through: a multiply-add by it stays one, so that
@@ -650,13 +652,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
         for (int i = 0; i < 16; i++) outp[db][i] = outg[db][i] = 0.f;
 
-    // YOSO-E: p = (base 2^kt)^tau <= 2^15, base = 1 - arccos(c)/pi.  Two polynomials, both
+    // YOSO-E: p = (base pbase)^tau < 2^16, base = 1 - arccos(c)/pi.  Two polynomials, both
     // least squares at Chebyshev nodes.  Where every |c| of a block is at most 1/2 (almost
     // all blocks of unclustered rows): 1/2 + arcsin(c)/pi = 1/2 + c A(c^2), A of degree 5,
     // |error| < 7e-9.  Else, with u = 1 - |c|: arccos(|c|)/pi = sqrt(u) Q(u), Q of degree 7,
     // relative error 2e-8.
-    const int kt = kExp ? 15 / args.tau : 0;
-    const float bs = ldexpf(1.0f, kt);
+    const float bs = args.pbase;
     constexpr float sq = kCosScale * kCosScale;  // a block's S is c * sq
     float ca[6] = {0.31830987334251404f, 0.05305203050374985f, 0.023855842649936676f,
                    0.014495517127215862f, 0.007610586937516928f, 0.013545230962336063f};
@@ -672,8 +673,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
         for (int i = 0; i < 8; i++) cq[i] *= bs;
     }
-    // W = G p wp: |G| < 2^22, p <= 2^(kt tau)
-    const float wp = ldexpf(1.0f, -(7 + kt * args.tau));
+    // W = G P 2^-7: |G| < 2^22, P <= 1
+    const float wp = ldexpf(args.pinv, -7);
     // *YOSO: x = S 2^(ex - 6) 2^(ey - 13); weight (s / pi) / sqrt(max(1 - x^2, 1/64)), at most s 2.55
     const float xs = kStar ? ldexpf(1.0f, ex - kFixedExp + ey - 13) : 0.f;
     const float sw = 0.31830988618379067f * ldexpf(1.0f, -(7 + kc + 2));
@@ -893,7 +894,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         if (frow < nf) {
             if constexpr (kP) {
                 const int e1 = kG ? eg : ey;
-                const float sc = kExp ? ldexpf(1.0f, e1 - 13 - kt * args.tau)
+                const float sc = kExp ? ldexpf(args.pinv, e1 - 13)
                                       : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + 7 + kc);
                 // (the dQ side of a launch for both sides has no P output)
                 if (a.out_p != nullptr) put(a.out_p, a.part_p, outp, sc);
@@ -1241,6 +1242,31 @@ hipError_t launch_tile_forward(const uint16_t *qcodes, const uint16_t *kcodes, c
     }
 }
 
+namespace {
+
+// The scale of YOSO-E's P before its split: the power of a factor pbase of the base.  P is at
+// most 1 and the pair ends at 2^-24, so pbase^tau lies just below fp16's largest number, for
+// every tau: a row whose cosines are all negative has only small P (2^15 a power of
+// two per factor leaves as little as 2^8 at tau = 8: Y of rows at cosines about -0.8 is then 1.6e-5
+// off instead of 1.7e-6).  pbase is a multiple of 1/32, so that half of it is exact, and pinv
+// divides by the power as the kernel rounds it, so that P = 1 comes out as 1.
+void expect_scale(TileArgs &a) {
+    auto power = [&](float x) {  // ipow's order of products
+        float r = x;
+        int bit = 16;
+        while (bit > a.tau) bit >>= 1;
+        for (bit >>= 1; bit > 0; bit >>= 1) r = (a.tau & bit) ? (r * r) * x : r * r;
+        return r;
+    };
+    int k = 32;
+    for (int step = 1 << 20; step > 0; step >>= 1)
+        if (power((k + step) / 32.0f) <= 65000.0f) k += step;
+    a.pbase = static_cast<float>(k) / 32.0f;
+    a.pinv = 1.0f / power(a.pbase);
+}
+
+}  // namespace
+
 hipError_t launch_expect_forward(const void *q, const void *k, const void *v, void *y, bool bf16, int64_t bh,
                                  int64_t n_q, int64_t n_k, int tau, hipStream_t stream) {
     if (bh == 0 || n_q == 0) return hipSuccess;
@@ -1249,6 +1275,7 @@ hipError_t launch_expect_forward(const void *q, const void *k, const void *v, vo
     a.side[0].fx = q; a.side[0].sx = k; a.side[0].sy = v; a.side[0].out_p = y;
     a.side[0].n_f = static_cast<int>(n_q); a.side[0].n_s = static_cast<int>(n_k);
     a.bh = bh; a.sides = 1; a.tau = tau; a.m = 1; a.split = 1;
+    expect_scale(a);
     return bf16 ? launch_tiles_alone<kWeightExpect, kSumP, true, 8>(a, stream, "expect_fwd_kernel")
                 : launch_tiles_alone<kWeightExpect, kSumP, false, 8>(a, stream, "expect_fwd_kernel");
 }
@@ -1267,6 +1294,7 @@ hipError_t launch_expect_backward(const void *q, const void *k, const void *v, c
     // keys fixed, queries streamed: dV and dK
     TileArgs a{};
     a.bh = bh; a.sides = 1; a.tau = tau; a.m = 1; a.split = 1;
+    expect_scale(a);
     TileSide &s = a.side[0];
     s.fx = k; s.fa = v; s.sx = q; s.sg = dy; s.sy = q; s.out_p = dv; s.out_g = dk;
     s.n_f = static_cast<int>(n_k); s.n_s = static_cast<int>(n_q);

@@ -89,6 +89,25 @@ def test_expectation_far_from_unit_scale(what, scale):
               TOL["f32"])
 
 
+@pytest.mark.parametrize("tau,cos", [(8, 0.8), (8, 0.9), (9, 0.8), (9, 0.9), (12, 0.7)])
+def test_expectation_opposite_rows(tau, cos):
+    """Queries and keys about two opposite directions (cosines about -cos): every row of Y and dV
+    consists of small P alone, down to about (0.144)^9 = 2^-25, whose fp16 (hi, lo) pairs end
+    at 2^-24 of a scale just below 2^16, i.e. at 2^-40 of P = 1: 2^-15 of such a P, and less
+    in the sum of a row."""
+    g = np.random.default_rng(700 + tau)
+    bh, nq, nk = 2, 300, 333
+    u = unit(g.standard_normal((bh, 1, 64)))
+    near = lambda n, s: unit(s * np.sqrt(cos) * u + np.sqrt(1 - cos) * unit(g.standard_normal((bh, n, 64))))
+    q, k = near(nq, 1.0), near(nk, -1.0)
+    v = g.standard_normal((bh, nk, 64))
+    dy = g.standard_normal((bh, nq, 64))
+    qd, kd, vd, dyd = (to_dev(a, "f32") for a in (q, k, v, dy))
+    y, _, _, dv = run_gpu(qd, kd, vd, dyd, tau)
+    ey, edv, _, _ = oracle.expectation(host(qd), host(kd), host(vd), host(dyd), tau)
+    check_all(f"yoso-e opposite tau{tau} cos -{cos}", [("y", y, ey), ("dv", dv, edv)], TOL["f32"])
+
+
 def test_expectation_closed_forms():
     """P = 1 for identical directions, 2^-tau for orthogonal ones, 0 for opposite ones."""
     tau = 5
