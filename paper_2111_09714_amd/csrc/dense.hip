@@ -54,6 +54,13 @@ enum : int { kSumP = 0, kSumPG = 1, kSumG = 2 };
 constexpr float kCosScale = 16.0f;   // cosine rows: unit length times 2^4
 constexpr int kFixedExp = 6;         // fixed rows: norm below 2^6
 constexpr float kNearFloor = 1.0f / 64.0f;  // *YOSO: 1 - x^2 is raised to at least 1/64
+// *YOSO: G (|G| < 2^22) enters the weights times 2^-kRowExp, which leaves the product of one
+// hash below 2^16.  Many hashes and small angles make a pair's weight up to 650 times that:
+// the weights are scaled per row to what comes (row_scale).  (With a scale for the worst that could
+// come an ordinary weight lay at 2^-3, 22 bits above the pair's end: dK of keys whose
+// queries have dY 10^4 below the head's largest was 7e-4 off, now 2e-5.)
+constexpr int kRowExp = 8;
+constexpr float kWeightMax = 32768.0f;
 
 struct TileSide {
     const void *fx, *fa;         // fixed side: cosine (or x) rows, rows of G
@@ -306,6 +313,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr bool kP = SUM != kSumG, kG = SUM != kSumP;
     constexpr bool kExp = WT == kWeightExpect, kStar = WT == kWeightStar;
     constexpr bool kX = WT != kWeightCount;  // a scalar product x beside G
+    constexpr bool kRowScale = kStar;        // weights with a factor per fixed row
     constexpr bool kOwnPlanes = !kExp && !kG;  // the forward: planes built here from the codes
     constexpr int PW = NW == 16 ? 2 : 1;       // word groups of 32 hashes
     constexpr int T = 8 * WAVES;             // streamed rows per tile
@@ -485,10 +493,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             }
         }
     }
-    // the largest count: m, or tau m times the largest weight 8/pi < 2.55
-    const int cmax = kStar ? args.tau * args.m : args.m;
     int kc = 0;
-    while ((1 << kc) < cmax) kc++;  // 2^kc >= cmax
+    while ((1 << kc) < args.m) kc++;  // 2^kc >= m
     // C is kept as C 2^-(7 + kc) (an exact fp16 number): |G| < 2^22, so W < 2^15; *YOSO keeps
     // N itself and scales the weight
     const float cscale = ldexpf(1.0f, -(7 + kc));
@@ -677,10 +683,51 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const float wp = ldexpf(args.pinv, -7);
     // *YOSO: x = S 2^(ex - 6) 2^(ey - 13); weight (s / pi) / sqrt(max(1 - x^2, 1/64)), at most s 2.55
     const float xs = kStar ? ldexpf(1.0f, ex - kFixedExp + ey - 13) : 0.f;
-    const float sw = 0.31830988618379067f * ldexpf(1.0f, -(7 + kc + 2));
+    const float sw = 0.31830988618379067f * ldexpf(1.0f, -kRowExp);
+
+    // fp32 sums of a pair of halves are taken per block first (one of 32 dims at a time) and
+    // then added to the running ones: an MFMA rounds its sum every 4 rows and there are three
+    // per product, and that many roundings of the large sums cost precision (dQ at 4096
+    // rows: error 6.0e-7 summed directly).  (YOSO-E's dK and dV have no registers for it; their
+    // error is P's.)
+    constexpr bool kTwoLevel = !BF16 && !(kExp && kP && kG);
+
+    // *YOSO: the lane's fixed row takes its weights times 2^-kw, or of one block times 1 / unscale
+    int kw = 0;
+    bool any_kw = false;  // some row of the wave has kw > 0
+    float unscale = 1.0f;
 
     const float zero = opaque(0.0f);
     auto split_w = [&](const float w[8], half8 &hi, half8 &lo) { split8_pk(w, 1.0f, hi, lo); };
+    // *YOSO's weights of a block (`most`: the lane's largest) in the window of their pairs.  Where
+    // the block's sums are taken apart (two levels), each row's are scaled by a power of two
+    // of their own, which the sums take back as they are added.  Else the row's factor falls
+    // when a weight would leave the window, and its running sums with it.
+    auto row_scale = [&](float most, floatx16 &w) {
+        if constexpr (!kTwoLevel) {
+            if (!any_kw && __builtin_amdgcn_ballot_w64(most > kWeightMax) == 0) return;
+        }
+        // (the halves of the wave hold the same fixed rows)
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
+        const float row = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        int e = 0;
+        if constexpr (kTwoLevel) {
+            frexpf(row, &e);  // row < 2^e
+            e = max(e - 15, -100);
+            unscale = ldexpf(1.0f, e);
+        } else {
+            if (ldexpf(row, -kw) > kWeightMax) frexpf(row, &e);
+            e = max(kw, e - 13);
+            const float f = ldexpf(1.0f, kw - e);
+#pragma unroll
+            for (int db = 0; db < 2; db++) outg[db] *= f;
+            kw = e;
+            any_kw = __builtin_amdgcn_ballot_w64(kw > 0) != 0;
+        }
+        const float f = ldexpf(1.0f, -e);
+#pragma unroll
+        for (int i = 0; i < 16; i++) w[i] *= f;
+    };
 
     // The products of a tile as a sequence of groups of one to three MFMAs on one operand
     // pair (hi, lo) from LDS: per block 4 groups of x and 4 of G (16 dims each), then 4 of the
@@ -793,12 +840,6 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                     default: ipow16<12>(p); break;
                 }
             }
-            // The sums.  fp32 sums of a pair of halves are taken per block first (one of 32 dims
-            // at a time) and then added to the running ones: an MFMA rounds its sum every 4
-            // rows and there are three per product, and that many roundings of the large sums
-            // cost precision (dQ at 4096 rows: error 6.0e-7 summed directly).
-            // (YOSO-E's dK and dV have no registers for it; their error is P's.)
-            constexpr bool kTwoLevel = !BF16 && !(kExp && kP && kG);
             // (hook0: the first of the hooks its four groups carry, `each` apiece, or -1)
             auto sums = [&](int gi0, int n, int hook0, int each, floatx16 (&out)[2], bool two, const half8 (&fh)[2],
                             const half8 (&fl)[2], bool pair) {
@@ -823,7 +864,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                             hook(h + 1, 1);
                         }
                     }
-                    if (two) out[db] += t;
+                    if (two) {
+                        if (kRowScale && n > 1 && &out == &outg) out[db] += t * unscale;
+                        else out[db] += t;
+                    }
                 }
             };
             // P as a pair (C, exact, as hi alone); the forward, which has no G, carries the next
@@ -845,23 +889,30 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                      kG || kX ? 1 : 2, outp, kTwoLevel && (kExp || !kG), ph, pl, kExp);
             }
             if constexpr (kG) {
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    if constexpr (kExp) {
+                        g[i] = g[i] * wp * p[i];
+                    } else if constexpr (kStar) {
+                        const float x = p[i] * xs;
+                        const float z = fmaxf(fmaf(-x, x, 1.0f), kNearFloor);
+                        g[i] *= static_cast<float>(c16[i >> 3][i & 7]) * (__builtin_amdgcn_rsqf(z) * sw);
+                    } else {
+                        g[i] = fmaf(g[i], static_cast<float>(c16[i >> 3][i & 7]), zero);
+                    }
+                }
+                if constexpr (kRowScale) {
+                    float most = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 16; i += 2) most = fmaxf(fmaxf(most, fabsf(g[i])), fabsf(g[i + 1]));
+                    row_scale(most, g);
+                }
                 half8 wh[2], wl[2];
 #pragma unroll
                 for (int s = 0; s < 2; s++) {
                     float w[8];
 #pragma unroll
-                    for (int e = 0; e < 8; e++) {
-                        const int i = 8 * s + e;
-                        if constexpr (kExp) {
-                            w[e] = g[i] * wp * p[i];
-                        } else if constexpr (kStar) {
-                            const float x = p[i] * xs;
-                            const float z = fmaxf(fmaf(-x, x, 1.0f), kNearFloor);
-                            w[e] = g[i] * (static_cast<float>(c16[s][e]) * (__builtin_amdgcn_rsqf(z) * sw));
-                        } else {
-                            w[e] = fmaf(g[i], static_cast<float>(c16[s][e]), zero);
-                        }
-                    }
+                    for (int e = 0; e < 8; e++) w[e] = g[8 * s + e];
                     split_w(w, wh[s], wl[s]);
                 }
                 sums(g0 + kPX + kPG + kPP, BF16 ? 2 : 3, 8 * k + 4, 1, outg, kTwoLevel, wh, wl, true);
@@ -903,7 +954,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 const int e = (eg - 13) + (ea - kFixedExp) + (ey - 13);
                 const float half_tau = 0.5f * static_cast<float>(args.tau);
                 const float sc = kExp    ? ldexpf(half_tau, e + 7)
-                                 : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + 7 + kc + 2)
+                                 : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + kRowExp + kw)
                                          : ldexpf(half_tau / static_cast<float>(args.m), e + 7 + kc);
                 put(a.out_g, a.part_g, outg, sc);
             }

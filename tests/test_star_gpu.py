@@ -75,6 +75,25 @@ def test_star_workload_full_size(name):
     check_all(f"star {name}", run(make_inputs(w), w.m, w.tau, w.dtype, heads=heads), TOL[w.dtype])
 
 
+@pytest.mark.parametrize("n,nk,m,tau,dist,what,scale", [
+    (700, 650, 32, 8, "gauss", "dy", 1e3),
+    (700, 650, 32, 8, "gauss", "dy", 1e4),
+    (700, 650, 32, 8, "gauss", "v", 1e4),
+    (300, 1100, 20, 12, "gauss", "dy", 1e4),    # twelve plane words
+    (600, 500, 64, 8, "gauss", "v", 1e4),       # two words per plane
+    (700, 650, 32, 8, "mixture", "dy", 1e4),    # hundreds of hashes and bits in one weight
+])
+def test_star_one_large_row(n, nk, m, tau, dist, what, scale):
+    """One row of dY (or V) far above the others: the rows of dK (or dQ) that it does not reach
+    consist of weights that far below the largest of their head, and keep the fp32 bar."""
+    name = f"star large {what} {scale:g} {n}x{nk} m{m} tau{tau} {dist}"
+    log(f"[{name}] start")
+    w = workloads.Workload(name, 1, 2, n, 64, tau, m, "f32", dist, 31000 + n + m)
+    inp = make_inputs(w, n=n, n_k=nk)
+    inp[what][:, inp[what].shape[1] // 2] *= scale
+    check_all(name, run(inp, m, tau, "f32"), TOL["f32"])
+
+
 def test_star_golden_worked_example(golden):
     g = golden["star_backward"]
     m, tau = g["m"], g["tau"]
