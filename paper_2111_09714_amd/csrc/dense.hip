@@ -28,7 +28,7 @@
 // this library; bf16 operands, scaled by powers of two, are exact as hi alone (cosine rows,
 // which are normalised, keep both).  Scales, all powers of two but the first:
 //   cosine rows     unit length times 2^4
-//   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e
+//   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e (counts: 2^(9 - e) and less)
 //   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan)
 //   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15;
 //                   P itself by pbase^tau, just below 2^16 (expect_scale)
@@ -53,6 +53,8 @@ enum : int { kSumP = 0, kSumPG = 1, kSumG = 2 };
 
 constexpr float kCosScale = 16.0f;   // cosine rows: unit length times 2^4
 constexpr int kFixedExp = 6;         // fixed rows: norm below 2^6
+constexpr int kFixedExpCount = 9;    // (weighted by counts: below 2^9, scaled down to 2^4 at most)
+constexpr int kCountExp = 11;        // counts: C 2^-11, exact fp16 numbers
 constexpr float kNearFloor = 1.0f / 64.0f;  // *YOSO: 1 - x^2 is raised to at least 1/64
 // *YOSO: G (|G| < 2^22) enters the weights times 2^-kRowExp, which leaves the product of one
 // hash below 2^16.  Many hashes and small angles make a pair's weight up to 650 times that:
@@ -313,7 +315,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr bool kP = SUM != kSumG, kG = SUM != kSumP;
     constexpr bool kExp = WT == kWeightExpect, kStar = WT == kWeightStar;
     constexpr bool kX = WT != kWeightCount;  // a scalar product x beside G
-    constexpr bool kRowScale = kStar;        // weights with a factor per fixed row
+    constexpr bool kRowScale = kStar;        // weights scaled per fixed row as they come
+    constexpr bool kCountG = kG && !kX;      // G weighted by counts
+    constexpr int kFE = kCountG ? kFixedExpCount : kFixedExp;
     constexpr bool kOwnPlanes = !kExp && !kG;  // the forward: planes built here from the codes
     constexpr int PW = NW == 16 ? 2 : 1;       // word groups of 32 hashes
     constexpr int T = 8 * WAVES;             // streamed rows per tile
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         if (ss > 0.f) frexpf(ss, &e2);  // ss < 2^e2: the norm is below 2^ceil(e2/2)
         ea = min(max((e2 + 1) >> 1, -60), 60);
 #pragma unroll
-        for (int s = 0; s < 4; s++) split8_pk(v[s], ldexpf(1.0f, kFixedExp - ea), arh[s], arl[s]);
+        for (int s = 0; s < 4; s++) split8_pk(v[s], ldexpf(1.0f, kFE - ea), arh[s], arl[s]);
     }
     if constexpr (kX) {
         float v[4][8], ss = 0.f;
@@ -450,7 +454,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             int e2 = 0;
             if (ss > 0.f) frexpf(ss, &e2);
             ex = min(max((e2 + 1) >> 1, -60), 60);
-            sc = ldexpf(1.0f, kFixedExp - ex);
+            sc = ldexpf(1.0f, kFE - ex);
         }
 #pragma unroll
         for (int s = 0; s < 4; s++) split8_pk(v[s], sc, xrh[s], xrl[s]);
@@ -493,11 +497,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             }
         }
     }
-    int kc = 0;
-    while ((1 << kc) < args.m) kc++;  // 2^kc >= m
-    // C is kept as C 2^-(7 + kc) (an exact fp16 number): |G| < 2^22, so W < 2^15; *YOSO keeps
-    // N itself and scales the weight
-    const float cscale = ldexpf(1.0f, -(7 + kc));
+    // C is kept as C 2^-11 (an exact fp16 number; *YOSO keeps N itself and scales the weight)
+    constexpr float cscale = 1.0f / (1 << kCountExp);
 
     __syncthreads();
     float hy = 0.f, hg = 0.f;
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     };
     half2v c2[2][4];
     uint32_t ueven[2] = {0u, 0u};
-    // (1024 + k) -> C 2^-(7 + kc) = (m - k) csc, or N = k (*YOSO), in one exact fp16 multiply-add
+    // (1024 + k) -> C 2^-11 = (m - k) csc, or N = k (*YOSO), in one exact fp16 multiply-add
     const float cm1 = kStar ? 1.0f : -cscale;
     const half2v cmul = {static_cast<_Float16>(cm1), static_cast<_Float16>(cm1)};
     const float ct1 = kStar ? -1024.0f : cscale * (1024.0f + static_cast<float>(args.m));
@@ -682,7 +683,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // W = G P 2^-7: |G| < 2^22, P <= 1
     const float wp = ldexpf(args.pinv, -7);
     // *YOSO: x = S 2^(ex - 6) 2^(ey - 13); weight (s / pi) / sqrt(max(1 - x^2, 1/64)), at most s 2.55
-    const float xs = kStar ? ldexpf(1.0f, ex - kFixedExp + ey - 13) : 0.f;
+    const float xs = kStar ? ldexpf(1.0f, ex - kFE + ey - 13) : 0.f;
     const float sw = 0.31830988618379067f * ldexpf(1.0f, -kRowExp);
 
     // fp32 sums of a pair of halves are taken per block first (one of 32 dims at a time) and
@@ -692,10 +693,44 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // error is P's.)
     constexpr bool kTwoLevel = !BF16 && !(kExp && kP && kG);
 
-    // *YOSO: the lane's fixed row takes its weights times 2^-kw, or of one block times 1 / unscale
+    // *YOSO: the lane's fixed row takes its weights times 2^-kw (fp32: of one block times 1 / unscale)
     int kw = 0;
     bool any_kw = false;  // some row of the wave has kw > 0
     float unscale = 1.0f;
+    // Counts: |G| < 2^25, so the weight G C 2^-11 of up to three hashes stays below 2^16, and a
+    // pair of one hash lies as high in the window as in the pair passes.  A row that meets a
+    // count of 4 or more is scaled down by 2^2, from a count of 16 on by as much as m takes,
+    // through its fixed row and with its running sums, before the tile's products.  The
+    // exponent field of C 2^-11 is 4 for C = 1, 5 for 2 and 3, 6 or 7 for 4 to 15, 8 to 10 from
+    // 16 on, so the bits of all counts of a row or'ed tell (`wmask`: those that ask for more).
+    // (One scale for a count of m, 2^-12 at m = 32, left rows whose partners lie 10^4 below the
+    // head's largest 4.8e-6 off in the median at 2048 rows, the pair passes 4.8e-7.)
+    uint32_t wmask = 0x28002800u;
+    auto count_kw = [&]() { return wmask == 0x28002800u ? 0 : wmask != 0 ? 2 : args.m < 64 ? 4 : 5; };
+    auto widen = [&](int bi) {
+        if constexpr (kCountG) {
+            u32x4 o4 = lds_get<u32x4>(ca_r[0] + bi * CB);
+#pragma unroll
+            for (int i = 1; i < T / 16; i++) o4 |= lds_get<u32x4>(ca_r[i] + bi * CB);
+            const uint32_t o = o4[0] | o4[1] | o4[2] | o4[3];
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64((o & wmask) != 0) == 0, 1)) return;
+            // (the halves of the wave hold the same fixed rows)
+            const auto r = __builtin_amdgcn_permlane32_swap(o, o, false, false);
+            const uint32_t both = r[0] | r[1];
+            const bool many = (both & 0x20002000u) != 0;
+            const int k0 = count_kw(), k = (both & wmask) == 0 ? k0 : !many ? 2 : args.m < 64 ? 4 : 5;
+            wmask = k == 0 ? 0x28002800u : k == 2 ? 0x20002000u : 0u;
+            const float f = ldexpf(1.0f, k0 - k);
+            const _Float16 fh = static_cast<_Float16>(f);
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                arh[s] *= fh;
+                if constexpr (!BF16) arl[s] *= fh;
+            }
+#pragma unroll
+            for (int db = 0; db < 2; db++) outg[db] *= f;
+        }
+    };
 
     const float zero = opaque(0.0f);
     auto split_w = [&](const float w[8], half8 &hi, half8 &lo) { split8_pk(w, 1.0f, hi, lo); };
@@ -705,7 +740,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // when a weight would leave the window, and its running sums with it.
     auto row_scale = [&](float most, floatx16 &w) {
         if constexpr (!kTwoLevel) {
-            if (!any_kw && __builtin_amdgcn_ballot_w64(most > kWeightMax) == 0) return;
+            if (__builtin_expect(!any_kw && __builtin_amdgcn_ballot_w64(most > kWeightMax) == 0, 1)) return;
         }
         // (the halves of the wave hold the same fixed rows)
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(most), __float_as_uint(most), false, false);
@@ -762,7 +797,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     };
     auto compute = [&](int bi, auto hook) {
         Op op[2];
+        // (beside the first operands' reads; where registers spill, before them: 51 -> 39 spills)
+        constexpr bool kWidenFirst = NW == 16 && kP && !BF16;
+        if (kWidenFirst) widen(bi);
         fetch(bi, 0, op[0]);
+        if (!kWidenFirst) widen(bi);
         // group gi of the tile: `mm(j, o)` issues its j-th MFMA; hook index hi (or -1)
         auto group = [&](int gi, int n, int hi, auto mm) {
             const Op &o = op[gi & 1];
@@ -946,16 +985,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             if constexpr (kP) {
                 const int e1 = kG ? eg : ey;
                 const float sc = kExp ? ldexpf(args.pinv, e1 - 13)
-                                      : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + 7 + kc);
+                                      : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + kCountExp);
                 // (the dQ side of a launch for both sides has no P output)
                 if (a.out_p != nullptr) put(a.out_p, a.part_p, outp, sc);
             }
             if constexpr (kG) {
-                const int e = (eg - 13) + (ea - kFixedExp) + (ey - 13);
+                const int e = (eg - 13) + (ea - kFE) + (ey - 13);
                 const float half_tau = 0.5f * static_cast<float>(args.tau);
                 const float sc = kExp    ? ldexpf(half_tau, e + 7)
                                  : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + kRowExp + kw)
-                                         : ldexpf(half_tau / static_cast<float>(args.m), e + 7 + kc);
+                                         : ldexpf(half_tau / static_cast<float>(args.m), e + kCountExp + count_kw());
                 put(a.out_g, a.part_g, outg, sc);
             }
         }

@@ -122,6 +122,56 @@ def test_star_tiles(bh, nq, nk, m, tau, dtype, tiles):
               [(n, host(o[sl]), r) for n, o, r in zip(("dq", "dk", "dv"), out, ref)], TOL[dtype])
 
 
+@pytest.mark.parametrize("n,nk,m,tau,what", [
+    (2048, 2048, 32, 8, "dy"), (2048, 2048, 32, 8, "v"), (700, 650, 32, 8, "dy"), (1500, 1200, 16, 11, "v"),
+    (1200, 1500, 64, 8, "dy"),
+])
+def test_backward_one_large_row(n, nk, m, tau, what):
+    """One row of dY (or V) 10^4 times the others: the rows of dK (or dQ) that it does not reach
+    consist of weights 2^13 below the largest of their head.  A weight of one hash is at least
+    about 2^8 in its fp16 pair's window, so then 2^-5, and ends at 2^-25: 2^-20 = 1e-6 of it,
+    and less of a row's sum."""
+    w = workloads.Workload("large", 1, 1, n, 64, tau, m, "f32", "gauss", 5100 + n + m)
+    inp = make_inputs(w, n=n, n_k=nk)
+    inp[what][:, inp[what].shape[1] // 2] *= 1e4
+    q, k, v, dy = (to_dev(inp[s], "f32") for s in ("q", "k", "v", "dy"))
+    qc, kc = Y.hash_qk(q, k, torch.from_numpy(inp["R"]).cuda(), m, tau)
+    out, ran = timed(FORMS, lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran["tile_kernel"] >= 1, ran
+    ref = oracle.backward(codes_np(qc), codes_np(kc), host(q), host(k), host(v), host(dy), m, tau)
+    got, want = (host(out[1])[0], ref[1][0]) if what == "dy" else (host(out[0])[0], ref[0][0])
+    size = np.linalg.norm(want, axis=-1)
+    err = (np.linalg.norm(got - want, axis=-1)[size > 0] / size[size > 0])
+    print(f"[large row {n}x{nk} m{m} tau{tau} {what}] median row error {np.median(err):.2e}")
+    assert np.median(err) < 1e-6, np.median(err)
+
+
+@pytest.mark.parametrize("m", [3, 15, 32, 63, 64])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("star", [False, True])
+def test_largest_weights(star, dtype, m):
+    """Every pair collides in every hash, V and dY rows of equal entries just below a power of
+    two: the scalar products and the counts at their bounds, the last keys also beside
+    pairs of a single hash."""
+    n, nk, tau = 300, 270, 8
+    g = np.random.default_rng(60 + m)
+    u = g.standard_normal(64)
+    q = np.tile(u / np.linalg.norm(u), (1, n, 1))
+    k = np.tile(u / np.linalg.norm(u), (1, nk, 1))
+    v, dy = np.full((1, nk, 64), 0.998), np.full((1, n, 64), -0.998)
+    q, k, v, dy = (to_dev(a, dtype) for a in (q, k, v, dy))
+    qc = torch.full((1, n, m), 5, dtype=torch.int16, device="cuda")
+    kc = torch.full((1, nk, m), 5, dtype=torch.int16, device="cuda")
+    kc[:, 200:, 1:] = 200
+    call = Y.backward_star if star else Y.backward
+    out, ran = timed(("tile_star_kernel", "tile_kernel"), lambda: call(qc, kc, q, k, v, dy, m, tau))
+    assert sum(ran.values()) >= 1, ran
+    ref = (oracle.backward_star if star else oracle.backward)(codes_np(qc), codes_np(kc), host(q), host(k), host(v),
+                                                              host(dy), m, tau)
+    check_all(f"largest weights {'star ' if star else ''}m{m} {dtype}",
+              [(s, host(o), r) for s, o, r in zip(("dq", "dk", "dv"), out, ref)], TOL[dtype])
+
+
 def test_bucket_tables_beside_the_tiles():
     """Clustered rows without a plane layout: the pair passes and the table form of the
     large buckets still serve them."""
