@@ -264,6 +264,36 @@ __device__ __forceinline__ void ipow16(floatx16 &p) {
     for (int i = 0; i < 16; i++) p[i] = ipow<N>(p[i]);
 }
 
+// Exponent e with amax < 2^e for any finite amax, at least -100 (0 for amax == 0): scales
+// 2^(13 - e) stay normal floats.
+__device__ __forceinline__ int scale_exp(float amax) {
+    int e = 0;
+    if (amax > 0.f) frexpf(amax, &e);
+    return max(e, -100);
+}
+
+// The same for the norm of a row held as 32 values each by lanes l and l ^ 32.  (The squares of
+// rows of any finite size overflow or vanish; those of rows scaled by their largest value
+// do not.)
+__device__ __forceinline__ int norm_exp(const float v[4][8]) {
+    float mx = 0.f;
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int i = 0; i < 8; i++) mx = fmaxf(mx, fabsf(v[s][i]));
+    const int e0 = scale_exp(fmaxf(mx, __shfl_xor(mx, 32)));
+    const float sc = ldexpf(1.0f, -e0);
+    float ss = 0.f;
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int i = 0; i < 8; i++) ss = fmaf(v[s][i] * sc, v[s][i] * sc, ss);
+    ss += __shfl_xor(ss, 32);
+    int e2 = 0;
+    if (ss > 0.f) frexpf(ss, &e2);  // ss < 2^e2: the norm is below 2^(e0 + ceil(e2/2))
+    return e0 + ((e2 + 1) >> 1);
+}
+
 // 8 values of a row as loaded
 template <bool BF16>
 struct Raw {
@@ -424,36 +454,28 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     half8 arh[4], arl[4], xrh[4], xrl[4];
     int ea = 0, ex = 0;
     if constexpr (kG) {
-        float v[4][8], ss = 0.f;
+        float v[4][8];
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            load8<BF16>(a.fa, foff + 16 * s, v[s]);
-#pragma unroll
-            for (int i = 0; i < 8; i++) ss = fmaf(v[s][i], v[s][i], ss);
-        }
-        ss += __shfl_xor(ss, 32);
-        int e2 = 0;
-        if (ss > 0.f) frexpf(ss, &e2);  // ss < 2^e2: the norm is below 2^ceil(e2/2)
-        ea = min(max((e2 + 1) >> 1, -60), 60);
+        for (int s = 0; s < 4; s++) load8<BF16>(a.fa, foff + 16 * s, v[s]);
+        ea = norm_exp(v);
 #pragma unroll
         for (int s = 0; s < 4; s++) split8_pk(v[s], ldexpf(1.0f, kFE - ea), arh[s], arl[s]);
     }
     if constexpr (kX) {
-        float v[4][8], ss = 0.f;
+        float v[4][8];
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            load8<BF16>(a.fx, foff + 16 * s, v[s]);
-#pragma unroll
-            for (int i = 0; i < 8; i++) ss = fmaf(v[s][i], v[s][i], ss);
-        }
-        ss += __shfl_xor(ss, 32);
+        for (int s = 0; s < 4; s++) load8<BF16>(a.fx, foff + 16 * s, v[s]);
         float sc;
         if constexpr (kExp) {
+            float ss = 0.f;
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int i = 0; i < 8; i++) ss = fmaf(v[s][i], v[s][i], ss);
+            ss += __shfl_xor(ss, 32);
             sc = ss > 0.f ? kCosScale / sqrtf(ss) : 0.f;
         } else {
-            int e2 = 0;
-            if (ss > 0.f) frexpf(ss, &e2);
-            ex = min(max((e2 + 1) >> 1, -60), 60);
+            ex = norm_exp(v);
             sc = ldexpf(1.0f, kFE - ex);
         }
 #pragma unroll
@@ -507,8 +529,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         hy = fmaxf(hy, wmax[0][w]);
         hg = fmaxf(hg, wmax[1][w]);
     }
-    const int ey = __builtin_amdgcn_readfirstlane(pow2_above(hy));
-    const int eg = kG ? __builtin_amdgcn_readfirstlane(pow2_above(hg)) : 0;
+    const int ey = __builtin_amdgcn_readfirstlane(scale_exp(hy));
+    const int eg = kG ? __builtin_amdgcn_readfirstlane(scale_exp(hg)) : 0;
     const float scy = ldexpf(1.0f, 13 - ey), scg = ldexpf(1.0f, 13 - eg);
 
     // convert and stage the tensor held in the raw registers (rows past cs1 as zeros)
@@ -961,15 +983,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 
     // ---- outputs
     auto finish = [&]() {
-        auto put = [&](void *dst, float *part, const floatx16 o[2], float sc) {
+        // o c 2^e (the power apart: it may pass the range of a scale where the output does not)
+        auto put = [&](void *dst, float *part, const floatx16 o[2], float c, int e) {
 #pragma unroll
             for (int db = 0; db < 2; db++)
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     // lane (l31, hh) holds out[row l31][32 db + 8 u + 4 hh + (0..3)] in registers 4u .. 4u+3
                     const int64_t off = (b * nf + frow) * D + 32 * db + 8 * u + 4 * hh;
-                    const float4 x = make_float4(o[db][4 * u] * sc, o[db][4 * u + 1] * sc, o[db][4 * u + 2] * sc,
-                                           o[db][4 * u + 3] * sc);
+                    const float4 x = make_float4(ldexpf(o[db][4 * u] * c, e), ldexpf(o[db][4 * u + 1] * c, e),
+                                                 ldexpf(o[db][4 * u + 2] * c, e), ldexpf(o[db][4 * u + 3] * c, e));
                     if (split > 1 || !BF16) {
                         *reinterpret_cast<float4 *>(split > 1 ? part + sp * (args.bh * nf * D) + off
                                                               : static_cast<float *>(dst) + off) = x;
@@ -984,18 +1007,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         if (frow < nf) {
             if constexpr (kP) {
                 const int e1 = kG ? eg : ey;
-                const float sc = kExp ? ldexpf(args.pinv, e1 - 13)
-                                      : ldexpf(1.0f / static_cast<float>(args.m), e1 - 13 + kCountExp);
                 // (the dQ side of a launch for both sides has no P output)
-                if (a.out_p != nullptr) put(a.out_p, a.part_p, outp, sc);
+                if (a.out_p != nullptr)
+                    put(a.out_p, a.part_p, outp, kExp ? args.pinv : 1.0f / static_cast<float>(args.m),
+                        e1 - 13 + (kExp ? 0 : kCountExp));
             }
             if constexpr (kG) {
                 const int e = (eg - 13) + (ea - kFE) + (ey - 13);
                 const float half_tau = 0.5f * static_cast<float>(args.tau);
-                const float sc = kExp    ? ldexpf(half_tau, e + 7)
-                                 : kStar ? ldexpf(1.0f / static_cast<float>(args.m), e + kRowExp + kw)
-                                         : ldexpf(half_tau / static_cast<float>(args.m), e + kCountExp + count_kw());
-                put(a.out_g, a.part_g, outg, sc);
+                if constexpr (kExp) put(a.out_g, a.part_g, outg, half_tau, e + 7);
+                else if constexpr (kStar)
+                    put(a.out_g, a.part_g, outg, 1.0f / static_cast<float>(args.m), e + kRowExp + kw);
+                else put(a.out_g, a.part_g, outg, half_tau / static_cast<float>(args.m), e + kCountExp + count_kw());
             }
         }
     };

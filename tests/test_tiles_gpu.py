@@ -146,6 +146,34 @@ def test_backward_one_large_row(n, nk, m, tau, what):
     assert np.median(err) < 1e-6, np.median(err)
 
 
+@pytest.mark.parametrize("what,scale", [("dy", 1e-25), ("v", 1e-25), ("dy", 1e-34), ("dy", 1e25), ("v", 1e30)])
+@pytest.mark.parametrize("kind,n,m", [("backward", 300, 32), ("backward", 1500, 16), ("star", 300, 32),
+                                      ("expectation", 300, 8)])
+def test_tiles_any_magnitude(kind, n, m, what, scale):
+    """dY or V of any finite size: the squares of such rows vanish or overflow, the rows' and
+    heads' powers of two do not."""
+    tau = 8
+    w = workloads.Workload("magnitude", 1, 1, n, 64, tau, m, "f32", "gauss", 8300 + n + m)
+    inp = make_inputs(w, n=n, n_k=n - 20)
+    inp[what] *= scale
+    q, k, v, dy = (to_dev(inp[s], "f32") for s in ("q", "k", "v", "dy"))
+    if kind == "expectation":
+        dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+        Y.yoso_expectation_backward(q, k, v, dy, tau, dq, dk, dv)
+        _, rv, rq, rk = oracle.expectation(host(q), host(k), host(v), host(dy), tau)
+    else:
+        qc, kc = Y.hash_qk(q, k, torch.from_numpy(inp["R"]).cuda(), m, tau)
+        call, ref = (Y.backward, oracle.backward) if kind == "backward" else (Y.backward_star, oracle.backward_star)
+        (dq, dk, dv), ran = timed(("tile_kernel", "tile_star_kernel"), lambda: call(qc, kc, q, k, v, dy, m, tau))
+        assert sum(ran.values()) >= 1, ran
+        rq, rk, rv = ref(codes_np(qc), codes_np(kc), host(q), host(k), host(v), host(dy), m, tau)
+    # (compared at the size of one: errors of values at 1e-34 square to nothing)
+    f = 1.0 / scale
+    check_all(f"magnitude {kind} {n} {what} {scale:g}",
+              [("dq", host(dq) * f, rq * f), ("dk", host(dk) * f, rk * f)] +
+              ([("dv", host(dv) * f, rv * f)] if what == "dy" and kind != "star" else []), TOL["f32"])
+
+
 @pytest.mark.parametrize("m", [3, 15, 32, 63, 64])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("star", [False, True])
