@@ -29,7 +29,9 @@
 // which are normalised, keep both).  Scales, all powers of two but the first:
 //   cosine rows     unit length times 2^4
 //   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e (counts: 2^(9 - e) and less)
-//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan)
+//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan);
+//                   those that counts alone weight (dV's dY, the forward's V) dim by dim, as
+//                   the bucket tables do, with the dims' powers taken back from a
 //   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15;
 //                   P itself by pbase^tau, just below 2^16 (expect_scale)
 #include <type_traits>
@@ -71,7 +73,8 @@ struct TileSide {
     const uint16_t *fcodes, *scodes;  // the codes [bh][n][m] themselves (forward, which has no scratch for planes)
     void *out_p, *out_g;         // P- (C-) weighted sum of sg (forward: of sy); G-weighted sum of sy
     float *part_p, *part_g;      // split > 1: their fp32 partial sums [split][bh][n_f][64]
-    const float *max_g, *max_y;  // partial maxima of |sg|, |sy| (kMaxParts per head, heads 4 kMaxParts apart), or null: scanned
+    // partial maxima of |sg|, |sy| ([kMaxParts][64] per head, heads 4 kMaxParts 64 apart), or null: scanned
+    const float *max_g, *max_y;
     int n_f, n_s;
 };
 
@@ -90,14 +93,31 @@ __device__ __forceinline__ float opaque(float x) {
     return x;
 }
 
+// Lane l holds values of dims 8 (l mod 8) + [0, 8): their maxima over the wave's rows (every lane).
+__device__ __forceinline__ void octet_max(float v[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        float x = v[i];
+        x = fmaxf(x, dpp_mov<0x128>(x));  // row_ror 8: lane l ^ 8
+        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        v[i] = fmaxf(__uint_as_float(c[0]), __uint_as_float(c[1]));
+    }
+}
+__device__ __forceinline__ void put_octet(float *row, int oct, const float v[8]) {
+    reinterpret_cast<float4 *>(row + 8 * oct)[0] = make_float4(v[0], v[1], v[2], v[3]);
+    reinterpret_cast<float4 *>(row + 8 * oct)[1] = make_float4(v[4], v[5], v[6], v[7]);
+}
+
 // The codes of both sides as bit planes [row][NW]: word t PW + w holds bit t of the codes
 // of hashes 32 w .. 32 w + 31 (PW = 2 for NW = 16, else 1); words past tau PW and bits past
 // m are zero.  One row per thread and word group w: the row's codes, 64 consecutive bytes,
 // are read once; 2 operations per code and bit (4 us at 2 x 131072 rows of 32 8-bit codes,
 // its traffic alone about 3).
 // Blocks past the planes' (`plane_blocks`) take partial maxima instead: block (b*4 + t)
-// kMaxParts + p writes max |x| over the p-th of kMaxParts row ranges of tensor t (0 Q, 1 dY,
-// 2 K, 3 V) of head b, from which the tiles derive their scales.
+// kMaxParts + p writes the largest |x| of each of the 64 dims over the p-th of kMaxParts row ranges
+// of tensor t (0 Q, 1 dY, 2 K, 3 V) of head b, from which the tiles derive their scales.
 template <int NW, bool BF16>
 __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restrict__ qcodes,
                                                         const uint16_t *__restrict__ kcodes,
@@ -116,7 +136,7 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
         const int64_t n = t < 2 ? n_q : n_k, per = (n + kMaxParts - 1) / kMaxParts;
         const int64_t r0 = min(n, p * per), r1 = min(n, r0 + per);
         const int64_t base = (b * n + r0) * D, count = (r1 - r0) * D;
-        float mx = 0.f;
+        float mx[8] = {};  // (a thread keeps to dims 8 (t mod 8) + [0, 8))
         for (int64_t e0 = static_cast<int64_t>(threadIdx.x) * 8; e0 < count; e0 += 256 * 8 * 4) {
             float x[4][8];
 #pragma unroll
@@ -127,13 +147,14 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
 #pragma unroll
             for (int u = 0; u < 4; u++)
 #pragma unroll
-                for (int i = 0; i < 8; i++) mx = fmaxf(mx, fabsf(x[u][i]));
+                for (int i = 0; i < 8; i++) mx[i] = fmaxf(mx[i], fabsf(x[u][i]));
         }
-        mx = wave_max(mx);
-        __shared__ float wred[4];
-        if ((threadIdx.x & 63) == 0) wred[threadIdx.x >> 6] = mx;
+        __shared__ __align__(16) float wred[4][D];
+        octet_max(mx);
+        if ((threadIdx.x & 63) < 8) put_octet(wred[threadIdx.x >> 6], threadIdx.x & 7, mx);
         __syncthreads();
-        if (threadIdx.x == 0) pmax[blk] = fmaxf(fmaxf(wred[0], wred[1]), fmaxf(wred[2], wred[3]));
+        const int d = threadIdx.x;
+        if (d < D) pmax[blk * D + d] = fmaxf(fmaxf(wred[0][d], wred[1][d]), fmaxf(wred[2][d], wred[3][d]));
         return;
     }
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -348,6 +369,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr bool kRowScale = kStar;        // weights scaled per fixed row as they come
     constexpr bool kCountG = kG && !kX;      // G weighted by counts
     constexpr int kFE = kCountG ? kFixedExpCount : kFixedExp;
+    // the rows that counts alone weight (dV's dY, the forward's V) are scaled dim by dim
+    constexpr bool kDims = kP && !kX;
     constexpr bool kOwnPlanes = !kExp && !kG;  // the forward: planes built here from the codes
     constexpr int PW = NW == 16 ? 2 : 1;       // word groups of 32 hashes
     constexpr int T = 8 * WAVES;             // streamed rows per tile
@@ -365,6 +388,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr int OSUM = kP && kG ? OG : OY;  // the first rows that sums read
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float wmax[2][WAVES];
+    __shared__ __align__(16) float dmax[kDims ? WAVES : 1][D];  // the waves' maxima per dim
+    __shared__ __align__(16) float dscale[kDims ? D + 8 : 4];   // 2^(13 - e_d); eight zeros
+    __shared__ __align__(16) int dexp[kDims ? D : 4];           // e_d: the dim's |values| are below 2^e_d
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bytes)smem));
 
     const int64_t t0 = (args.side[0].n_f + 32 * WAVES - 1) / (32 * WAVES);
@@ -412,12 +438,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 
     // ---- the streamed tensors' largest |value| over the head (every split scans all of
     // it, so that the scales, and the results, do not depend on the share)
-    float mg = 0.f, my = 0.f;
+    float mg = 0.f, my = 0.f, md[8] = {};
     const bool have_max = a.max_y != nullptr;
     if (have_max) {
-        const int64_t e = b * 4 * kMaxParts + (lane & (kMaxParts - 1));
-        my = a.max_y[e];
-        if constexpr (kG) mg = a.max_g[e];
+        const int64_t e = b * (4 * kMaxParts * D) + 8 * lane;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            my = fmaxf(my, a.max_y[e + i]);
+            if constexpr (kG) mg = fmaxf(mg, a.max_g[e + i]);
+        }
+        if constexpr (kDims) {
+            // (lane: dims 8 (lane mod 8) + [0, 8) of part lane / 8)
+            static_assert(kMaxParts == 8, "a part per eight lanes");
+            const float *src = kG ? a.max_g : a.max_y;
+#pragma unroll
+            for (int i = 0; i < 8; i++) md[i] = src[e + i];
+        }
     }
     for (int c = have_max ? ns : srow; c < ns; c += 4 * T) {
         Raw<BF16> u[4], w[4];
@@ -432,15 +468,30 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             float v[8];
             raw_values<BF16>(u[i], v);
 #pragma unroll
-            for (int e = 0; e < 8; e++) my = fmaxf(my, fabsf(v[e]));
+            for (int e = 0; e < 8; e++) {
+                if constexpr (kDims && !kG) md[e] = fmaxf(md[e], fabsf(v[e]));
+                else my = fmaxf(my, fabsf(v[e]));
+            }
             if constexpr (kG) {
                 raw_values<BF16>(w[i], v);
 #pragma unroll
-                for (int e = 0; e < 8; e++) mg = fmaxf(mg, fabsf(v[e]));
+                for (int e = 0; e < 8; e++) {
+                    if constexpr (kDims) md[e] = fmaxf(md[e], fabsf(v[e]));
+                    else mg = fmaxf(mg, fabsf(v[e]));
+                }
             }
         }
     }
     load_part(cs0, 0);
+    if constexpr (kDims) {
+        octet_max(md);
+        if (lane < 8) put_octet(dmax[wave], lane, md);
+        float m = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; i++) m = fmaxf(m, md[i]);
+        if constexpr (kG) mg = m;
+        else my = m;
+    }
     my = wave_max(my);
     if constexpr (kG) mg = wave_max(mg);
     if (lane == 0) {
@@ -453,13 +504,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const int64_t foff = (b * nf + min(frow, nf - 1)) * D + 8 * hh;
     half8 arh[4], arl[4], xrh[4], xrl[4];
     int ea = 0, ex = 0;
+    float va[kG ? 4 : 1][8];
+    auto fix_a = [&]() {
+        if constexpr (kG) {
+            ea = norm_exp(va);
+#pragma unroll
+            for (int s = 0; s < 4; s++) split8_pk(va[s], ldexpf(1.0f, kFE - ea), arh[s], arl[s]);
+        }
+    };
     if constexpr (kG) {
-        float v[4][8];
 #pragma unroll
-        for (int s = 0; s < 4; s++) load8<BF16>(a.fa, foff + 16 * s, v[s]);
-        ea = norm_exp(v);
-#pragma unroll
-        for (int s = 0; s < 4; s++) split8_pk(v[s], ldexpf(1.0f, kFE - ea), arh[s], arl[s]);
+        for (int s = 0; s < 4; s++) load8<BF16>(a.fa, foff + 16 * s, va[s]);
+        if constexpr (!kDims) fix_a();
     }
     if constexpr (kX) {
         float v[4][8];
@@ -532,6 +588,25 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const int ey = __builtin_amdgcn_readfirstlane(scale_exp(hy));
     const int eg = kG ? __builtin_amdgcn_readfirstlane(scale_exp(hg)) : 0;
     const float scy = ldexpf(1.0f, 13 - ey), scg = ldexpf(1.0f, 13 - eg);
+    if constexpr (kDims) {
+        if (tid < D + 8) {
+            float m = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; w++) m = fmaxf(m, dmax[w][tid & (D - 1)]);
+            const int e = m > 0.f ? scale_exp(m) : -100;  // (a dim of zeros: nothing of a)
+            dscale[tid] = tid < D ? ldexpf(1.0f, 13 - e) : 0.f;
+            if (tid < D) dexp[tid] = e;
+        }
+        __syncthreads();
+        // G = a . g: what scales a dim of g is taken back from a (up to the head's power)
+        if constexpr (kG) {
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int i = 0; i < 8; i++) va[s][i] = ldexpf(va[s][i], dexp[16 * s + 8 * hh + i] - eg);
+            fix_a();
+        }
+    }
 
     // convert and stage the tensor held in the raw registers (rows past cs1 as zeros)
     const uint32_t st_h = lane_base(lds0 + srow * 256 + ((soct ^ tswz(srow)) << 4));
@@ -553,7 +628,21 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             lds_put<half8>(st_h + t, h);
             if (lo_too) lds_put<half8>(st_l + t, l);
         };
-        if (part == 0) put(OY + bi * TB, raw, scy, !BF16, false);
+        auto put_dims = [&](uint32_t t) {
+            float v[8];
+            raw_values<BF16>(raw, v);
+            const float *sc = dscale + (ok ? 8 * soct : D);
+            const float4 s0 = reinterpret_cast<const float4 *>(sc)[0], s1 = reinterpret_cast<const float4 *>(sc)[1];
+            v[0] *= s0.x; v[1] *= s0.y; v[2] *= s0.z; v[3] *= s0.w;
+            v[4] *= s1.x; v[5] *= s1.y; v[6] *= s1.z; v[7] *= s1.w;
+            half8 h, l;
+            split8_pk(v, 1.0f, h, l);
+            lds_put<half8>(st_h + t, h);
+            if (!BF16) lds_put<half8>(st_l + t, l);
+        };
+        if (kDims && !kG) put_dims(OY + bi * TB);
+        else if (part == 0) put(OY + bi * TB, raw, scy, !BF16, false);
+        else if (kDims && part == 1) put_dims(OG + bi * TB);
         else if (kG && part == 1) put(OG + bi * TB, raw, scg, !BF16, false);
         else put(OX + bi * TB, raw, 1.0f, true, true);
     };
@@ -984,15 +1073,20 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // ---- outputs
     auto finish = [&]() {
         // o c 2^e (the power apart: it may pass the range of a scale where the output does not)
-        auto put = [&](void *dst, float *part, const floatx16 o[2], float c, int e) {
+        auto put = [&](void *dst, float *part, const floatx16 o[2], float c, int e0, bool dims) {
 #pragma unroll
             for (int db = 0; db < 2; db++)
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     // lane (l31, hh) holds out[row l31][32 db + 8 u + 4 hh + (0..3)] in registers 4u .. 4u+3
                     const int64_t off = (b * nf + frow) * D + 32 * db + 8 * u + 4 * hh;
-                    const float4 x = make_float4(ldexpf(o[db][4 * u] * c, e), ldexpf(o[db][4 * u + 1] * c, e),
-                                                 ldexpf(o[db][4 * u + 2] * c, e), ldexpf(o[db][4 * u + 3] * c, e));
+                    int4 e = make_int4(e0, e0, e0, e0);
+                    if (dims) {
+                        const int4 ed = reinterpret_cast<const int4 *>(dexp)[8 * db + 2 * u + hh];
+                        e = make_int4(e0 + ed.x, e0 + ed.y, e0 + ed.z, e0 + ed.w);
+                    }
+                    const float4 x = make_float4(ldexpf(o[db][4 * u] * c, e.x), ldexpf(o[db][4 * u + 1] * c, e.y),
+                                                 ldexpf(o[db][4 * u + 2] * c, e.z), ldexpf(o[db][4 * u + 3] * c, e.w));
                     if (split > 1 || !BF16) {
                         *reinterpret_cast<float4 *>(split > 1 ? part + sp * (args.bh * nf * D) + off
                                                               : static_cast<float *>(dst) + off) = x;
@@ -1006,19 +1100,19 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         };
         if (frow < nf) {
             if constexpr (kP) {
-                const int e1 = kG ? eg : ey;
+                const int e1 = kDims ? 0 : kG ? eg : ey;
                 // (the dQ side of a launch for both sides has no P output)
                 if (a.out_p != nullptr)
                     put(a.out_p, a.part_p, outp, kExp ? args.pinv : 1.0f / static_cast<float>(args.m),
-                        e1 - 13 + (kExp ? 0 : kCountExp));
+                        e1 - 13 + (kExp ? 0 : kCountExp), kDims);
             }
             if constexpr (kG) {
                 const int e = (eg - 13) + (ea - kFE) + (ey - 13);
                 const float half_tau = 0.5f * static_cast<float>(args.tau);
-                if constexpr (kExp) put(a.out_g, a.part_g, outg, half_tau, e + 7);
+                if constexpr (kExp) put(a.out_g, a.part_g, outg, half_tau, e + 7, false);
                 else if constexpr (kStar)
-                    put(a.out_g, a.part_g, outg, 1.0f / static_cast<float>(args.m), e + kRowExp + kw);
-                else put(a.out_g, a.part_g, outg, half_tau / static_cast<float>(args.m), e + kCountExp + count_kw());
+                    put(a.out_g, a.part_g, outg, 1.0f / static_cast<float>(args.m), e + kRowExp + kw, false);
+                else put(a.out_g, a.part_g, outg, half_tau / static_cast<float>(args.m), e + kCountExp + count_kw(), false);
             }
         }
     };
@@ -1275,7 +1369,7 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t nq = rows_q * D, nk = rows_k * D;
-    auto pmax = [&](int i) { return plan.maxima ? t.pmax + i * kMaxParts : nullptr; };
+    auto pmax = [&](int i) { return plan.maxima ? t.pmax + i * kMaxParts * D : nullptr; };
     TileArgs a{};
     a.bh = t.bh; a.m = t.m; a.tau = t.tau;
     TileSide kv{}, q{};

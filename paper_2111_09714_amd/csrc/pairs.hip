@@ -2314,7 +2314,9 @@ bool tile_star_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
 }
 
 // The dense tiles of dense.hip on this layout's scratch: the planes (at most 64 bytes per
-// row) take the space of the fp16 copies (256 bytes), partial outputs that of the partial rows.
+// row) take the space of the fp16 copies of Q and K (256 bytes), the maxima (8 KiB per head, only
+// where a side has 128 rows or more: 32 KiB) that of dY or V, partial outputs that of the
+// partial rows.
 hipError_t launch_tiles_on(const uint16_t *qcodes, const uint16_t *kcodes, const void *q, const void *k, const void *v,
                            const void *dy, bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool star,
                            void *dq, void *dk, void *dv, const BackwardLayout &L, unsigned char *ws,
@@ -2325,7 +2327,7 @@ hipError_t launch_tiles_on(const uint16_t *qcodes, const uint16_t *kcodes, const
     t.bh = bh; t.n_q = n_q; t.n_k = n_k; t.m = m; t.tau = tau; t.star = star;
     t.qpl = reinterpret_cast<uint32_t *>(ws + L.qs);
     t.kpl = reinterpret_cast<uint32_t *>(ws + L.ks);
-    t.pmax = reinterpret_cast<float *>(ws + L.pmax);
+    t.pmax = reinterpret_cast<float *>(ws + (n_q >= n_k ? L.dys : L.vs));
     t.part = reinterpret_cast<float *>(ws + L.pq);
     t.part_bytes = L.pmax - L.pq;
     return launch_tile_backward(t, bf16, stream);

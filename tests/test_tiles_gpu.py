@@ -146,6 +146,40 @@ def test_backward_one_large_row(n, nk, m, tau, what):
     assert np.median(err) < 1e-6, np.median(err)
 
 
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype", [
+    (2, 2048, 1500, 32, 8, "f32"),        # maxima from the prep launch
+    (1, 1200, 1100, 16, 9, "f32"),        # both sides in one launch
+    (96, 1030, 600, 32, 10, "f32"),       # scanned by each workgroup; the forward in tiles as well
+    (96, 1030, 600, 32, 10, "bf16"),
+])
+def test_tiles_resolve_every_feature_dim(bh, nq, nk, m, tau, dtype):
+    """Feature dims of very different scales (10^-4 .. 10^4, and one of zeros): each dim has its own
+    power of two, as in the bucket tables, so each column of Y and dV meets the bar on its
+    own; dQ and dK, sums over all dims, meet it as a whole."""
+    w = workloads.Workload("dims", 1, bh, nq, 64, tau, m, dtype, "gauss", 640 + nq)
+    inp = make_inputs(w, n=nq, n_k=nk)
+    g = np.random.default_rng(6)
+    for key in ("v", "dy"):
+        scales = 10.0 ** g.permutation(np.linspace(-4, 4, 64))
+        scales[7] = 0.0
+        inp[key] = inp[key] * scales
+    q, k, v, dy = (to_dev(inp[s], dtype) for s in ("q", "k", "v", "dy"))
+    qc, kc = Y.hash_qk(q, k, torch.from_numpy(inp["R"]).cuda(), m, tau)
+    y = Y.forward(qc, kc, v, m, tau)
+    (dq, dk, dv), ran = timed(FORMS, lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran["tile_kernel"] >= 1, ran
+    sl = [0]
+    ry = oracle.forward(codes_np(qc[sl]), codes_np(kc[sl]), host(v[sl]), m, tau)
+    rq, rk, rv = oracle.backward(codes_np(qc[sl]), codes_np(kc[sl]), host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]),
+                                 m, tau)
+    for name, got, ref in (("y", host(y[sl])[0], ry[0]), ("dv", host(dv[sl])[0], rv[0])):
+        size = np.linalg.norm(ref, axis=0)
+        col = np.linalg.norm(got - ref, axis=0) / np.where(size > 0, size, 1.0)
+        print(f"[dims {bh}x{nq}x{nk} {dtype}] {name}: worst column {col.max():.2e}")
+        assert col.max() <= TOL[dtype], (name, col.max())
+    check_all(f"dims {bh}x{nq}x{nk} {dtype}", [("dq", host(dq[sl]), rq), ("dk", host(dk[sl]), rk)], TOL[dtype])
+
+
 @pytest.mark.parametrize("what,scale", [("dy", 1e-25), ("v", 1e-25), ("dy", 1e-34), ("dy", 1e25), ("v", 1e30)])
 @pytest.mark.parametrize("kind,n,m", [("backward", 300, 32), ("backward", 1500, 16), ("star", 300, 32),
                                       ("expectation", 300, 8)])
