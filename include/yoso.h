@@ -344,7 +344,8 @@ const char *yoso_last_error(void);
  * frees them).  yoso_timing_reset() forgets the launches recorded so far.
  * yoso_timing_query() waits for the recorded events of `kernel` ("hash_kernel",
  * "fast_hash_kernel", "fast_hyperplanes_kernel", "table_kernel", "sort_kernel", "split_kernel", "pass_kernel", "bucket_kernel",
- * "reduce_kernel", "dense_kernel", "dense_fwd_kernel", "tile_prep_kernel", "tile_kernel",
+ * "reduce_kernel", "dense_kernel", "dense_fwd_kernel" (the forward in either dense form),
+ * "tile_fwd_kernel" (in tiles), "tile_prep_kernel", "tile_kernel",
  * "tile_star_kernel", "pass_star_kernel", "dense_sum_kernel", "zero_kernel", "l2norm_kernel", "l2norm_bwd_kernel", "expect_fwd_kernel",
  * "expect_bwd_kv_kernel", "expect_bwd_q_kernel")
  * and returns the summed duration and the launch count.

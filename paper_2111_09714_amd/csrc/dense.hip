@@ -1438,6 +1438,7 @@ hipError_t launch_tile_forward(const uint16_t *qcodes, const uint16_t *kcodes, c
     a.bh = bh; a.sides = 1; a.m = m; a.tau = tau;
     auto go = [&](auto nw) {
         constexpr int NW = decltype(nw)::value;
+        KernelTimer timer("tile_fwd_kernel", stream);  // (beside the name that both dense forms share)
         return bf16 ? launch_tiles_alone<kWeightCount, kSumP, true, NW>(a, stream, "dense_fwd_kernel")
                     : launch_tiles_alone<kWeightCount, kSumP, false, NW>(a, stream, "dense_fwd_kernel");
     };
