@@ -2535,7 +2535,12 @@ bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m
     const int nw = tile_plane_words(m, tau);
     const int64_t blocks = bh * ((n_q + 127) / 128);
     if (nw == 0 || n_k == 0 || blocks < 256) return false;
-    if (dense_forward_applies(bh, n_q, n_k, m, tau)) return true;  // (against the 16 x 16 form)
+    // Against the 16 x 16 form: at most 64 queries fill half a workgroup of the tiles and one of that
+    // form, whose blocks take half the pairs (16 x 16 / tiles, us, fp32: 4096 x 8 x 16 33 / 57, 1024 x
+    // 64 x 64 17 / 23, x 200 37 / 42, x 1000 133 / 152; bf16: x 64 16 / 19, x 128 24 / 25, x 200 37 / 34;
+    // m = 64: x 64 28 / 31, x 128 41 / 42, 600 heads 35 / 32).  From 65 on the tiles: 992 x 65 34 / 25.
+    if (dense_forward_applies(bh, n_q, n_k, m, tau))
+        return n_q > 64 || (n_k > 128 && (bf16 || nw == 16));
     const double tiles = (bf16 ? 7.0e-7 : 8.0e-7) * (nw == 8 ? 1.0 : nw == 12 ? 1.45 : 1.75) *
                          static_cast<double>(n_q) * n_k;
     return tiles * (blocks >= 768 ? 1.0 : blocks >= 512 ? 1.3 : 1.8) <=

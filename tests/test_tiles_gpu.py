@@ -270,6 +270,29 @@ def test_expectation_tiles(bh, nq, nk, tau, dtype):
               TOL[dtype])
 
 
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,form", [
+    (520, 64, 97, 8, 5, "f32", "16 x 16"),       # half of a workgroup of the tiles
+    (520, 65, 97, 8, 5, "f32", "tiles"),
+    (520, 64, 128, 32, 8, "bf16", "16 x 16"),
+    (520, 20, 129, 32, 8, "bf16", "tiles"),
+    (300, 20, 129, 32, 8, "f32", "tiles"),       # too few heads for the 16 x 16 form
+    (520, 30, 200, 64, 8, "f32", "tiles"),       # two words per plane
+    (520, 30, 200, 32, 10, "f32", "16 x 16"),
+    (256, 100, 64, 12, 8, "f32", "16 x 16"),     # m not a multiple of 8
+    (4, 1500, 1500, 32, 8, "f32", "tables"),     # few heads
+])
+def test_forward_rule(bh, nq, nk, m, tau, dtype, form):
+    """The forward's three forms on either side of their rules.  (A launch of the tiles counts as
+    dense_fwd_kernel, like one of the 16 x 16 form, and as tile_fwd_kernel.)"""
+    (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype)
+    names = ("dense_fwd_kernel", "tile_fwd_kernel", "table_kernel")
+    y, ran = timed(names, lambda: Y.forward(qc, kc, v, m, tau, n_q=nq))
+    assert ran == dict(zip(names, {"tiles": (1, 1, 0), "16 x 16": (1, 0, 0), "tables": (0, 0, 1)}[form])), ran
+    sl = [0, bh - 1]
+    ref = oracle.forward(codes_np(qc[sl]), codes_np(kc[sl]), host(v[sl]), m, tau)
+    check_all(f"forward {form} bh{bh} {nq}x{nk} m{m} tau{tau} {dtype}", [("y", host(y[sl]), ref)], TOL[dtype])
+
+
 @pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,kernel", [
     (520, 65, 97, 8, 5, "f32", "tile"),        # 8 waves; a partial word of hashes
     (300, 130, 31, 32, 8, "bf16", "tile"),
