@@ -347,7 +347,7 @@ const char *yoso_last_error(void);
  * "reduce_kernel", "dense_kernel", "dense_fwd_kernel" (the forward in either dense form),
  * "tile_fwd_kernel" (in tiles), "tile_prep_kernel", "tile_kernel",
  * "tile_star_kernel", "pass_star_kernel", "dense_sum_kernel", "zero_kernel", "l2norm_kernel", "l2norm_bwd_kernel", "expect_fwd_kernel",
- * "expect_bwd_kv_kernel", "expect_bwd_q_kernel")
+ * "expect_bwd_kv_kernel", "expect_bwd_q_kernel", "expect_blocks_kernel" (any of these three in the form for short sides))
  * and returns the summed duration and the launch count.
  * Not thread-safe with respect to concurrent launches on other threads' streams
  * beyond the pool bookkeeping, which is locked.

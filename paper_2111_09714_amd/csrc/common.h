@@ -175,6 +175,14 @@ __device__ __forceinline__ int pow2_above(float amax) {
     return min(max(e, -60), 60);
 }
 
+// Exponent e with amax < 2^e for any finite amax, at least -100 (0 for amax == 0): scales
+// 2^(13 - e) stay normal floats.
+__device__ __forceinline__ int scale_exp(float amax) {
+    int e = 0;
+    if (amax > 0.f) frexpf(amax, &e);
+    return max(e, -100);
+}
+
 // Workgroups are dispatched to the 8 XCDs round-robin (id % 8).  Remap so that
 // consecutive logical ids land on the same XCD and share its L2; the mapping is
 // a bijection on [0, n) for any n.

@@ -285,15 +285,7 @@ __device__ __forceinline__ void ipow16(floatx16 &p) {
     for (int i = 0; i < 16; i++) p[i] = ipow<N>(p[i]);
 }
 
-// Exponent e with amax < 2^e for any finite amax, at least -100 (0 for amax == 0): scales
-// 2^(13 - e) stay normal floats.
-__device__ __forceinline__ int scale_exp(float amax) {
-    int e = 0;
-    if (amax > 0.f) frexpf(amax, &e);
-    return max(e, -100);
-}
-
-// The same for the norm of a row held as 32 values each by lanes l and l ^ 32.  (The squares of
+// scale_exp for the norm of a row held as 32 values each by lanes l and l ^ 32.  (The squares of
 // rows of any finite size overflow or vanish; those of rows scaled by their largest value
 // do not.)
 __device__ __forceinline__ int norm_exp(const float v[4][8]) {
@@ -1479,6 +1471,12 @@ hipError_t launch_expect_forward(const void *q, const void *k, const void *v, vo
                                  int64_t n_q, int64_t n_k, int tau, hipStream_t stream) {
     if (bh == 0 || n_q == 0) return hipSuccess;
     if (n_k == 0) return zero_rows_async(y, bh * n_q * D * (bf16 ? 2 : 4), stream);
+    if (expect_blocks_apply(kExpectForward, bf16, bh, n_q, n_k)) {
+        ExpectBlocks e{};
+        e.xr = q; e.xc = k; e.yc = v; e.out1 = y;
+        e.bh = bh; e.n_r = static_cast<int>(n_q); e.n_c = static_cast<int>(n_k); e.tau = tau;
+        return launch_expect_blocks(kExpectForward, e, bf16, stream);
+    }
     TileArgs a{};
     a.side[0].fx = q; a.side[0].sx = k; a.side[0].sy = v; a.side[0].out_p = y;
     a.side[0].n_f = static_cast<int>(n_q); a.side[0].n_s = static_cast<int>(n_k);
@@ -1499,6 +1497,8 @@ hipError_t launch_expect_backward(const void *q, const void *k, const void *v, c
         if ((err = zero_rows_async(dk, bh * n_k * D * e, stream)) != hipSuccess) return err;
         return zero_rows_async(dv, bh * n_k * D * e, stream);
     }
+    ExpectBlocks x{};
+    x.bh = bh; x.tau = tau;
     // keys fixed, queries streamed: dV and dK
     TileArgs a{};
     a.bh = bh; a.sides = 1; a.tau = tau; a.m = 1; a.split = 1;
@@ -1506,10 +1506,21 @@ hipError_t launch_expect_backward(const void *q, const void *k, const void *v, c
     TileSide &s = a.side[0];
     s.fx = k; s.fa = v; s.sx = q; s.sg = dy; s.sy = q; s.out_p = dv; s.out_g = dk;
     s.n_f = static_cast<int>(n_k); s.n_s = static_cast<int>(n_q);
-    err = bf16 ? launch_tiles_alone<kWeightExpect, kSumPG, true, 8>(a, stream, "expect_bwd_kv_kernel")
-               : launch_tiles_alone<kWeightExpect, kSumPG, false, 8>(a, stream, "expect_bwd_kv_kernel");
+    if (expect_blocks_apply(kExpectKV, bf16, bh, n_k, n_q)) {
+        x.xr = k; x.ar = v; x.xc = q; x.bc = dy; x.yc = q; x.out1 = dv; x.out2 = dk;
+        x.n_r = static_cast<int>(n_k); x.n_c = static_cast<int>(n_q);
+        err = launch_expect_blocks(kExpectKV, x, bf16, stream);
+    } else {
+        err = bf16 ? launch_tiles_alone<kWeightExpect, kSumPG, true, 8>(a, stream, "expect_bwd_kv_kernel")
+                   : launch_tiles_alone<kWeightExpect, kSumPG, false, 8>(a, stream, "expect_bwd_kv_kernel");
+    }
     if (err != hipSuccess) return err;
     // queries fixed, keys streamed: dQ
+    if (expect_blocks_apply(kExpectQ, bf16, bh, n_q, n_k)) {
+        x.xr = q; x.ar = dy; x.xc = k; x.bc = v; x.yc = k; x.out1 = nullptr; x.out2 = dq;
+        x.n_r = static_cast<int>(n_q); x.n_c = static_cast<int>(n_k);
+        return launch_expect_blocks(kExpectQ, x, bf16, stream);
+    }
     s = TileSide{};
     s.fx = q; s.fa = dy; s.sx = k; s.sg = v; s.sy = k; s.out_g = dq;
     s.n_f = static_cast<int>(n_q); s.n_s = static_cast<int>(n_k);

@@ -60,6 +60,18 @@ hipError_t launch_expect_backward(const void *q, const void *k, const void *v, c
                                   void *dv, bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int tau,
                                   hipStream_t stream);
 
+// YOSO-E for short sides (expect.hip): one launch of the forward, of dK with dV, or of dQ
+enum : int { kExpectForward = 0, kExpectKV = 1, kExpectQ = 2 };
+struct ExpectBlocks {
+    const void *xr, *ar;       // fixed side: rows whose cosines are taken; rows of G (backward)
+    const void *xc, *bc, *yc;  // streamed side: cosine rows; G rows (backward); rows that are summed
+    void *out1, *out2;         // P-weighted sum (forward, dV); G-weighted sum (dK, dQ)
+    int64_t bh;
+    int n_r, n_c, tau;
+};
+bool expect_blocks_apply(int mode, bool bf16, int64_t bh, int64_t n_r, int64_t n_c);
+hipError_t launch_expect_blocks(int mode, const ExpectBlocks &a, bool bf16, hipStream_t stream);
+
 constexpr int kMaxParts = 8;  // partial maxima per (head, tensor)
 
 // fp32 partial outputs [split][count4 groups of four], summed in split order

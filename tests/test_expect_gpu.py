@@ -108,6 +108,32 @@ def test_expectation_opposite_rows(tau, cos):
     check_all(f"yoso-e opposite tau{tau} cos -{cos}", [("y", y, ey), ("dv", dv, edv)], TOL["f32"])
 
 
+@pytest.mark.parametrize("bh,nq,nk,tau,dtype,blocks", [
+    (600, 64, 64, 8, "f32", 3), (600, 17, 63, 9, "bf16", 3), (3, 64, 32, 12, "f32", 2),   # (dK, dV stream 64 rows)
+    (3, 1, 7, 3, "bf16", 3), (3, 63, 65, 8, "f32", 0), (2, 300, 17, 8, "f32", 2), (600, 65, 66, 8, "f32", 0),
+])
+def test_expectation_short_sides(bh, nq, nk, tau, dtype, blocks):
+    """Few streamed rows, or up to 64 fixed ones in many heads, take a form of their own (`blocks` of the three
+    launches), rows of every size among them."""
+    g = np.random.default_rng(500 + nq + nk + tau)
+    q, k = unit(g.standard_normal((bh, nq, 64))), unit(g.standard_normal((bh, nk, 64)))
+    v = g.standard_normal((bh, nk, 64)) * 10.0 ** g.uniform(-3, 1, size=(bh, nk, 1))
+    dy = g.standard_normal((bh, nq, 64)) * 1e-30
+    qd, kd, vd, dyd = (to_dev(a, dtype) for a in (q, k, v, dy))
+    Y.yoso_timing_enable(64)
+    Y.yoso_timing_reset()
+    try:
+        y, dq, dk, dv = run_gpu(qd, kd, vd, dyd, tau)
+        assert Y.yoso_timing_query("expect_blocks_kernel")[1] == blocks
+    finally:
+        Y.yoso_timing_enable(0)
+    sl = [0, bh - 1]
+    ey, edv, edq, edk = oracle.expectation(host(qd)[sl], host(kd)[sl], host(vd)[sl], host(dyd)[sl], tau)
+    check_all(f"yoso-e short bh{bh} {nq}x{nk} tau{tau} {dtype}",
+              [("y", y[sl], ey), ("dq", dq[sl] * 1e30, edq * 1e30), ("dk", dk[sl] * 1e30, edk * 1e30),
+               ("dv", dv[sl] * 1e30, edv * 1e30)], TOL[dtype])
+
+
 def test_expectation_closed_forms():
     """P = 1 for identical directions, 2^-tau for orthogonal ones, 0 for opposite ones."""
     tau = 5
