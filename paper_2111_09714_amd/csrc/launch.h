@@ -99,9 +99,8 @@ struct TileBackward {
 };
 int tile_plane_words(int m, int tau);  // 0: these codes have no plane layout
 hipError_t launch_tile_backward(const TileBackward &t, bool bf16, hipStream_t stream);
-// Streamed rows that a CU visits one after another in yoso_backward's launches of the tiles
-// (dK and dV 0.54 of the time, dQ 0.46): their time up to a factor.
-double tile_rows(int64_t bh, int64_t n_q, int64_t n_k);
+// microseconds of yoso_backward in tiles with `room` bytes for partial outputs
+double tile_cost(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, size_t room);
 
 // The forward over every pair in dense tiles: codes it can take, and the launch (n_k > 0).
 bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau);

@@ -2267,38 +2267,47 @@ namespace {
 // *YOSO always takes the pair passes.
 bool dense_form(int64_t n_q, int64_t n_k, bool star) { return !star && n_q <= kDenseMaxN && n_k <= kDenseMaxN; }
 
-// The dense tiles (dense.hip) visit every (query, key) pair; the pair and table forms
-// visit the colliding ones but pay for a partial row per row and hash.  Both are priced in
-// microseconds, fitted to 1 to 64 heads of 1100 to 8000 rows (fp32, 32 heads, m = 32, tau =
-// 8: 2048 rows 627 us in pairs against 268 in tiles, 4096: 1413 / 978, 6000: 2343 / 2099; m =
-// 8, 2048 rows: 342 / 259, 4096: 799 / 967; 64 x 1100, m = 4: 203 / 268; bf16 32 x 4096: 932 /
-// 678; 1 x 2048: 127 / 44):
-//   tiles  per streamed row and round of workgroups, by plane words and storage;
-//   pairs  per row (both sides) a fixed share and one per hash, and per colliding pair of
-//          uniform codes.
+// Microseconds of the backward in the pair and table forms, fitted like tile_cost (half of the
+// shapes within 8%, nine in ten within 25%).  A (head, hash) unit takes its time however many there
+// are: per row of either side and per pair of uniform codes, a bucket of the table form as its
+// rows; a full card takes the units' work: per row, per row and hash, per pair.  Tables of more
+// than 2^10 buckets take several passes.
+double pair_cost(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
+    const double B = static_cast<double>(1 << tau), bq = static_cast<double>(n_q) / B, bk = static_cast<double>(n_k) / B;
+    const double pairs = B * fmin(bq * bk, kTableT * (bq + bk));
+    const double units = static_cast<double>(bh) * m, rows = static_cast<double>(n_q + n_k);
+    const double lo = static_cast<double>(n_q < n_k ? n_q : n_k), hi = rows - lo;
+    const double one = bf16 ? 0.0242 * hi + 0.0113 * lo + 1.4e-4 * pairs : 0.0282 * hi + 0.0137 * lo + 3.1e-4 * pairs;
+    const double all = bf16 ? 3.0e-4 * bh * rows + 9.3e-5 * units * rows + 2.2e-6 * units * pairs
+                            : 5.0e-4 * bh * rows + 1.23e-4 * units * rows + 4.2e-6 * units * pairs;
+    const double passes = tau > 10 ? 43.0 + 0.63 * units : 0.0;
+    // (past 8192 rows the tables' dV rounds less than the tiles': there the tiles take only what
+    // the work alone decides)
+    if (hi > 8192.0) return 76.0 + all + passes;
+    return 26.0 + sqrt(one * one + all * all) + passes;
+}
+
+// The dense tiles (dense.hip) visit every (query, key) pair; the pair and table forms visit the
+// colliding ones but pay for a partial row per row and hash.  Pairs / tiles, us, fp32, m = 32, tau =
+// 8 unless said: 32 x 2048 627 / 268, 32 x 4096 1413 / 1020, 1 x 2048 127 / 33, 4 x 8100 642 / 597; m = 8:
+// 32 x 1200 136 / 180, 8 x 3000 169 / 202; m = 4: 64 x 1100 170 / 254, 1 x 4096 205 / 130; m = 2, tau =
+// 10: 4 x 8100 361 / 755, 32 x 1200 129 / 199.
 // Short sequences (both sides at most kDenseMaxN rows) have the 16 x 16 dense form instead of
-// the pairs (us, that form / tiles): 384 x 512 497 / 286, 12 x 512 48 / 32, 1 x 1024 43 / 26, 1 x 512
-// 27.5 / 19.2, 1 x 256 23.4 / 18.2, 1 x 64 17.7 / 15.5, 128 x 64 27.4 / 15.4; with fewer rows on a
-// side and few pairs both are launches only (1 x 32: 16.0 / 15.3).
+// the pairs (us, that form / tiles): 384 x 512 497 / 295, 12 x 512 48 / 32, 1 x 1024 43 / 26, 1 x 512
+// 27.5 / 19.2, 1 x 256 23.4 / 18.2, 1 x 64 17.7 / 15.5, 128 x 64 27.4 / 15.4, 4096 x 1 x 200 846 / 432; with
+// fewer rows on a side and few pairs both are launches only (1 x 32: 16.0 / 15.3).
 bool tile_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool bf16) {
     const int nw = tile_plane_words(m, tau);
     if (nw == 0 || n_q == 0 || n_k == 0 || bh == 0) return false;
-    const double pairs = static_cast<double>(n_q) * n_k, heads = static_cast<double>(bh);
-    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN && heads * pairs >= 524288.0) return true;
+    const double pairs = static_cast<double>(bh) * n_q * n_k;
+    // (the 16 x 16 form sums every pair as well: few rows on a side are no less precise here)
+    if (n_q <= kDenseMaxN && n_k <= kDenseMaxN && pairs >= 524288.0) return true;
     // (a few rows against a long side: most rows have a single partner, whose scalar product
     // decides the row's precision; the pairs' two chains of 32 dims round it less often)
     if (n_q < 64 || n_k < 64) return false;
     if (n_q <= kDenseMaxN && n_k <= kDenseMaxN) return true;
-    const double words = nw == 8 ? 1.0 : nw == 12 ? 1.18 : 1.62;
-    const double tiles = (bf16 ? 0.083 : 0.119) * words * tile_rows(bh, n_q, n_k) + 25.0;
-    const double rows = static_cast<double>(n_q + n_k);
-    // (fewer than some 128 (head, hash) units leave CUs without one: 1 x 8192 540 us in pairs, 174
-    // in tiles, 4 x 8192 615 / 582.  Past 8192 rows the tables' dV rounds less than the tiles')
-    const bool idle = heads * m < 128.0 && n_q <= 8192 && n_k <= 8192;
-    const double busy = idle ? 128.0 / m : heads;
-    const double colliding = busy * ((bf16 ? 5.3e-4 : 1.0e-3) * rows + (bf16 ? 8.5e-5 : 9.7e-5) * m * rows) +
-                             heads * (bf16 ? 1.0e-6 : 5.4e-6) * m * pairs / static_cast<double>(1 << tau);
-    return tiles <= colliding + 50.0;
+    const BackwardLayout L = backward_layout(bf16, bh, n_q, n_k, m, tau);
+    return tile_cost(bf16, bh, n_q, n_k, m, tau, L.pmax - L.pq) <= pair_cost(bf16, bh, n_q, n_k, m, tau);
 }
 
 // *YOSO on the tiles: one visit of a pair takes all its hashes, against partial rows and

@@ -84,6 +84,12 @@ BACKWARD = [
     (32, 1024, 1024, 32, 8, "bf16", "tile_kernel", None),
     (1, 1100, 1100, 34, 9, "f32", "pass_kernel", None),     # no plane layout: pairs
     (32, 3000, 3000, 2, 10, "bf16", "pass_kernel", None),   # few hashes: pairs
+    (32, 1200, 1200, 2, 10, "f32", "pass_kernel", None),
+    (64, 1100, 1100, 4, 8, "f32", "pass_kernel", None),
+    (4, 4000, 4000, 2, 10, "f32", "pass_kernel", None),     # (no scratch to split the rows)
+    (1, 300, 8000, 4, 8, "f32", "pass_kernel", None),       # a short side beside a long one
+    (4, 8000, 500, 2, 6, "bf16", "pass_kernel", None),
+    (1024, 1, 512, 32, 8, "f32", "tile_kernel", False),     # many heads of a few rows: no pairs there
 ]
 
 
