@@ -101,6 +101,7 @@ int tile_plane_words(int m, int tau);  // 0: these codes have no plane layout
 hipError_t launch_tile_backward(const TileBackward &t, bool bf16, hipStream_t stream);
 // microseconds of yoso_backward in tiles with `room` bytes for partial outputs
 double tile_cost(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, size_t room);
+double tile_star_cost(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, size_t room);  // of *YOSO's dQ, dK
 
 // The forward over every pair in dense tiles: codes it can take, and the launch (n_k > 0).
 bool tile_forward_applies(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau);

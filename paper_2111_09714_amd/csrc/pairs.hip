@@ -2310,16 +2310,32 @@ bool tile_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool bf16) 
     return tile_cost(bf16, bh, n_q, n_k, m, tau, L.pmax - L.pq) <= pair_cost(bf16, bh, n_q, n_k, m, tau);
 }
 
-// *YOSO on the tiles: one visit of a pair takes all its hashes, against partial rows and
-// pairs of m tau derived hashes (fp32, 16 x 2000, m = 32, tau = 8: 3606 against 270 us; 4
-// heads of 16384 rows, m = 4, tau = 12: 1950 against 4700, on the pairs' side of the line).
-bool tile_star_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
+// Microseconds of *YOSO's dQ and dK in pairs, fitted like tile_star_cost (half within 12%): a derived
+// (head, hash) unit's time, and the work of all m tau of a head.
+double pair_star_cost(bool bf16, int64_t bh, int64_t n_q, int64_t n_k, int m, int tau) {
+    const double pairs = static_cast<double>(n_q) * n_k / static_cast<double>(1 << (tau - 1));
+    const double units = static_cast<double>(bh) * m * tau, rows = static_cast<double>(n_q + n_k);
+    const double lo = static_cast<double>(n_q < n_k ? n_q : n_k), hi = rows - lo;
+    const double one = (bf16 ? 0.0281 * hi + 0.0097 * lo : 0.0347 * hi + 0.0134 * lo) + 3.1e-4 * pairs;
+    const double all = units * ((bf16 ? 1.3e-4 : 2.3e-4) * rows + 3.0e-6 * pairs + 0.01);
+    return 40.0 + sqrt(one * one + all * all);
+}
+
+// *YOSO on the tiles: one visit of a pair takes all its hashes, against partial rows and pairs of
+// m tau derived hashes.  Pairs / tiles, us, fp32: 16 x 2000, m = 32, tau = 8 3606 / 274; by the work of a
+// full card 4 heads of 16384 rows, m = 4, tau = 12 1950 / 4700; a short side beside a long one leaves
+// the tiles' workgroups few and long, against the units of the pairs: 1 x 64 x 32000, m = 4, tau = 12
+// 1378 / 3711, 2 x 5 x 5000, m = 2, tau = 10 247 / 596, m = 32, tau = 8 503 / 360.
+bool tile_star_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool bf16) {
     const int nw = tile_plane_words(m, tau);
     if (nw == 0 || n_q == 0 || n_k == 0 || bh == 0) return false;
     const double pairs = static_cast<double>(n_q) * n_k, derived = static_cast<double>(m) * tau;
     const double tiles = (nw == 8 ? 3.3e-6 : nw == 12 ? 4.5e-6 : 6.0e-6) * pairs;
-    return tiles <= derived * (2.0e-4 * static_cast<double>(n_q + n_k) +
-                               2.8e-6 * pairs / static_cast<double>(1 << (tau - 1)));
+    if (tiles > derived * (2.0e-4 * static_cast<double>(n_q + n_k) + 2.8e-6 * pairs / static_cast<double>(1 << (tau - 1))))
+        return false;
+    const BackwardLayout L = backward_layout(bf16, bh, n_q, n_k, m * tau, tau - 1);
+    return tile_star_cost(bf16, bh, n_q, n_k, m, tau, L.pmax - L.pq) <=
+           1.05 * pair_star_cost(bf16, bh, n_q, n_k, m, tau);
 }
 
 // The dense tiles of dense.hip on this layout's scratch: the planes (at most 64 bytes per
@@ -2604,7 +2620,7 @@ hipError_t launch_backward_star(const uint16_t *qcodes, const uint16_t *kcodes, 
     // dV: eq. (gradient-v), as in launch_backward
     hipError_t e = launch_table(qcodes, dy, kcodes, dv, bf16, bh, n_q, n_k, m, tau, ws + S.table, stream);
     if (e != hipSuccess) return e;
-    if (tile_star_form(bh, n_q, n_k, m, tau))
+    if (tile_star_form(bh, n_q, n_k, m, tau, bf16))
         return launch_tiles_on(qcodes, kcodes, q, k, v, dy, bf16, bh, n_q, n_k, m, tau, true, dq, dk, nullptr, S.pairs, ws,
                                stream);
     uint16_t *qd = reinterpret_cast<uint16_t *>(ws + S.qcodes), *kd = reinterpret_cast<uint16_t *>(ws + S.kcodes);

@@ -115,6 +115,9 @@ def test_backward_tiles(bh, nq, nk, m, tau, dtype, form, split):
     (1, 500, 1030, 60, 8, "bf16", True),
     (1, 300, 290, 40, 12, "f32", False),     # no plane layout
     (1, 4000, 4000, 1, 4, "f32", False),     # one hash: few derived hashes
+    (16, 100, 4000, 2, 10, "bf16", False),   # few and long workgroups of the tiles
+    (4, 8000, 500, 4, 8, "bf16", False),
+    (1, 300, 8000, 32, 8, "f32", True),
 ])
 def test_star_tiles(bh, nq, nk, m, tau, dtype, tiles):
     (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype, "mixture")
