@@ -29,7 +29,8 @@
 // which are normalised, keep both).  Scales, all powers of two but the first:
 //   cosine rows     unit length times 2^4
 //   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e (counts: 2^(9 - e) and less)
-//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan);
+//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan;
+//                   YOSO-E: a tile of 32 or 64 rows far below its head by its own e);
 //                   those that counts alone weight (dV's dY, the forward's V) dim by dim, as
 //                   the bucket tables do, with the dims' powers taken back from a
 //   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15;
@@ -378,8 +379,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr int OX0 = 0, OG = kExp ? 2 * TB : 0, OY = OG + (kG ? 2 * TB : 0), OX = kStar ? OY : OX0;
     constexpr int OC = OY + 2 * TB, OP = OC + 2 * CB;
     constexpr int OSUM = kP && kG ? OG : OY;  // the first rows that sums read
+    constexpr int OT = OY + 2 * TB;  // YOSO-E: a word per tile of each streamed tensor (sy, then sg)
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float wmax[2][WAVES];
+    __shared__ int wfar[WAVES];  // YOSO-E: a tile far below its head
     __shared__ __align__(16) float dmax[kDims ? WAVES : 1][D];  // the waves' maxima per dim
     __shared__ __align__(16) float dscale[kDims ? D + 8 : 4];   // 2^(13 - e_d); eight zeros
     __shared__ __align__(16) int dexp[kDims ? D : 4];           // e_d: the dim's |values| are below 2^e_d
@@ -432,6 +435,44 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // it, so that the scales, and the results, do not depend on the share)
     float mg = 0.f, my = 0.f, md[8] = {};
     const bool have_max = a.max_y != nullptr;
+    // YOSO-E: of each tile of T rows, too (words at OT); a wave takes 64 rows at a time
+    const int ntiles = kExp ? (ns + T - 1) / T : 0;
+    if constexpr (kExp) {
+        for (int g0 = 64 * wave; g0 < ns; g0 += 64 * WAVES) {
+            Raw<BF16> u[8], w[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const int64_t off = (b * ns + min(g0 + 8 * i + (lane >> 3), ns - 1)) * D + 8 * (lane & 7);
+                raw_load<BF16>(u[i], a.sy, off);
+                if constexpr (kG) raw_load<BF16>(w[i], a.sg, off);
+            }
+#pragma unroll
+            for (int h = 0; h < 64 / T; h++) {
+                float ty = 0.f, tg = 0.f;
+#pragma unroll
+                for (int i = h * (T / 8); i < (h + 1) * (T / 8); i++) {
+                    float v[8];
+                    raw_values<BF16>(u[i], v);
+#pragma unroll
+                    for (int e = 0; e < 8; e++) ty = fmaxf(ty, fabsf(v[e]));
+                    if constexpr (kG) {
+                        raw_values<BF16>(w[i], v);
+#pragma unroll
+                        for (int e = 0; e < 8; e++) tg = fmaxf(tg, fabsf(v[e]));
+                    }
+                }
+                ty = wave_max(ty);
+                if constexpr (kG) tg = wave_max(tg);
+                const int tile = g0 / T + h;
+                if (lane == 0 && tile < ntiles) {
+                    lds_put<float>(lds0 + OT + 4 * tile, ty);
+                    if constexpr (kG) lds_put<float>(lds0 + OT + 4 * (ntiles + tile), tg);
+                }
+                my = fmaxf(my, ty);
+                mg = fmaxf(mg, tg);
+            }
+        }
+    }
     if (have_max) {
         const int64_t e = b * (4 * kMaxParts * D) + 8 * lane;
 #pragma unroll
@@ -447,7 +488,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             for (int i = 0; i < 8; i++) md[i] = src[e + i];
         }
     }
-    for (int c = have_max ? ns : srow; c < ns; c += 4 * T) {
+    for (int c = have_max || kExp ? ns : srow; c < ns; c += 4 * T) {
         Raw<BF16> u[4], w[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -580,6 +621,27 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const int ey = __builtin_amdgcn_readfirstlane(scale_exp(hy));
     const int eg = kG ? __builtin_amdgcn_readfirstlane(scale_exp(hg)) : 0;
     const float scy = ldexpf(1.0f, 13 - ey), scg = ldexpf(1.0f, 13 - eg);
+    // YOSO-E: the exponents of the tiles.  A tile keeps its head's until its largest value is 2^8
+    // below (then it has 30 bits left above the pairs' end), and follows it down to 2^40.
+    bool varied = false;  // (no tile has: nothing of this in the loop)
+    if constexpr (kExp) {
+        bool far = false;
+        for (int i = tid; i < (kG ? 2 : 1) * ntiles; i += 64 * WAVES) {
+            const float m = lds_get<float>(lds0 + OT + 4 * i);
+            const int head = i < ntiles ? ey : eg, e = m > 0.f ? scale_exp(m) : head;
+            far = far || e < head - 8;
+            lds_put<int>(lds0 + OT + 4 * i, e < head - 8 ? max(e, head - 40) : head);
+        }
+        const bool any = __builtin_amdgcn_ballot_w64(far) != 0;
+        if (lane == 0) wfar[wave] = any ? 1 : 0;
+        __syncthreads();
+        int f = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) f |= wfar[w];
+        varied = __builtin_amdgcn_readfirstlane(f) != 0;
+    }
+    auto tile_y = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (c0 / T)); };
+    auto tile_g = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (ntiles + c0 / T)); };
     if constexpr (kDims) {
         if (tid < D + 8) {
             float m = 0.f;
@@ -633,9 +695,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             if (!BF16) lds_put<half8>(st_l + t, l);
         };
         if (kDims && !kG) put_dims(OY + bi * TB);
-        else if (part == 0) put(OY + bi * TB, raw, scy, !BF16, false);
+        else if (part == 0) put(OY + bi * TB, raw, varied ? ldexpf(1.0f, 13 - tile_y(c0)) : scy, !BF16, false);
         else if (kDims && part == 1) put_dims(OG + bi * TB);
-        else if (kG && part == 1) put(OG + bi * TB, raw, scg, !BF16, false);
+        else if (kG && part == 1) put(OG + bi * TB, raw, varied ? ldexpf(1.0f, 13 - tile_g(c0)) : scg, !BF16, false);
         else put(OX + bi * TB, raw, 1.0f, true, true);
     };
 
@@ -1062,6 +1124,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         }
     };
 
+    int cy = ey, cg = eg;  // the exponents that the running sums are in
+
     // ---- outputs
     auto finish = [&]() {
         // o c 2^e (the power apart: it may pass the range of a scale where the output does not)
@@ -1092,14 +1156,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         };
         if (frow < nf) {
             if constexpr (kP) {
-                const int e1 = kDims ? 0 : kG ? eg : ey;
+                const int e1 = kDims ? 0 : kG ? cg : cy;
                 // (the dQ side of a launch for both sides has no P output)
                 if (a.out_p != nullptr)
                     put(a.out_p, a.part_p, outp, kExp ? args.pinv : 1.0f / static_cast<float>(args.m),
                         e1 - 13 + (kExp ? 0 : kCountExp), kDims);
             }
             if constexpr (kG) {
-                const int e = (eg - 13) + (ea - kFE) + (ey - 13);
+                const int e = (cg - 13) + (ea - kFE) + (cy - 13);
                 const float half_tau = 0.5f * static_cast<float>(args.tau);
                 if constexpr (kExp) put(a.out_g, a.part_g, outg, half_tau, e + 7, false);
                 else if constexpr (kStar)
@@ -1147,6 +1211,23 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         const int c1 = min(c0 + T, clast), c2n = min(c0 + 2 * T, clast), c3 = min(c0 + 3 * T, clast);
         Words w[2];
         load_words(w[0], nxt, 0);
+        if (kExp && __builtin_expect(varied, 0)) {
+            // the running sums in the tile's units
+            const int ty = __builtin_amdgcn_readfirstlane(tile_y(c0));
+            const int tg = kG ? __builtin_amdgcn_readfirstlane(tile_g(c0)) : 0;
+            if (__builtin_expect(ty != cy || tg != cg, 0)) {
+                const int dy = cy - ty, dg = cg - tg;
+#pragma unroll
+                for (int db = 0; db < 2; db++)
+#pragma unroll
+                    for (int i = 0; i < 16; i++) {
+                        if constexpr (kP) outp[db][i] = ldexpf(outp[db][i], kG ? dg : dy);
+                        if constexpr (kG) outg[db][i] = ldexpf(outg[db][i], dy + dg);
+                    }
+                cy = ty;
+                cg = tg;
+            }
+        }
         compute(cur, [&](int i, int half) {
             if (half == 0) {
                 if (i + 1 < NSL) load_words(w[(i + 1) & 1], nxt, i + 1);
@@ -1257,9 +1338,11 @@ template <int WT, int SUM, bool BF16, int NW, int WAVES>
 hipError_t launch_tiles_w(const TileArgs &a, hipStream_t stream, const char *name) {
     const int64_t blocks = side_blocks(a, 32 * WAVES) * a.split;
     if (blocks == 0) return hipSuccess;
+    // (YOSO-E: a word per tile of each streamed tensor, at most 16 KiB)
+    const int words = WT == kWeightExpect ? (SUM == kSumP ? 1 : 2) * ((a.side[0].n_s + 8 * WAVES - 1) / (8 * WAVES)) : 0;
     KernelTimer timer(name, stream);
     hipLaunchKernelGGL((tile_kernel<WT, SUM, BF16, NW, WAVES>), dim3(static_cast<unsigned>(blocks)), dim3(64 * WAVES),
-                       (tile_lds<WT, SUM, NW, WAVES>()), stream, a);
+                       (tile_lds<WT, SUM, NW, WAVES>() + 4 * words), stream, a);
     return hipGetLastError();
 }
 

@@ -189,6 +189,33 @@ def test_tiles_resolve_every_feature_dim(bh, nq, nk, m, tau, dtype):
     check_all(f"dims {bh}x{nq}x{nk} {dtype}", [("dq", host(dq[sl]), rq), ("dk", host(dk[sl]), rk)], TOL[dtype])
 
 
+@pytest.mark.parametrize("bh,nq,nk,tau", [(1, 300, 5, 8), (2, 333, 290, 8), (300, 300, 130, 8), (1, 1000, 1500, 9)])
+@pytest.mark.parametrize("ratio", [1e-7, 1e-4])
+def test_expectation_rows_far_apart(bh, nq, nk, tau, ratio):
+    """Two opposite groups of rows (cosines about -0.95 between them, P down to 1e-9), the first with
+    dY and V `ratio` times the second's: a run of small rows has scales of its own (per tile of
+    32 or 64 rows), so sums that the large ones hardly reach keep the bar."""
+    g = np.random.default_rng(9100 + nq)
+    unit = lambda a: a / np.linalg.norm(a, axis=-1, keepdims=True)
+    u = unit(g.standard_normal((bh, 1, 64)))
+    side = lambda n: np.where(np.arange(n) < n // 2, 1.0, -1.0)[None, :, None]
+    rows = lambda n: unit(side(n) * np.sqrt(0.97) * u + np.sqrt(0.03) * unit(g.standard_normal((bh, n, 64))))
+    size = lambda n: np.where(np.arange(n) < n // 2, ratio, 1.0)[None, :, None]
+    q, k = rows(nq), rows(nk)
+    v, dy = g.standard_normal((bh, nk, 64)) * size(nk), g.standard_normal((bh, nq, 64)) * size(nq)
+    q, k, v, dy = (to_dev(a, "f32") for a in (q, k, v, dy))
+    y, dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    Y.yoso_expectation_forward(q, k, v, tau, y)
+    Y.yoso_expectation_backward(q, k, v, dy, tau, dq, dk, dv)
+    sl = [0, bh - 1] if bh > 1 else [0]
+    ey, edv, _, _ = oracle.expectation(host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]), tau)
+    # (each group's rows of Y and dV are mostly sums of their own group's)
+    for name, got, ref, n in (("y", y, ey, nq), ("dv", dv, edv, nk)):
+        d = np.linalg.norm(host(got[sl]) - ref, axis=-1)[:, :n // 2] / np.linalg.norm(ref, axis=-1)[:, :n // 2]
+        print(f"[far apart {bh}x{nq}x{nk} tau{tau} {ratio:g}] {name}: worst small row {d.max(initial=0):.2e}")
+        assert d.max(initial=0) < 1e-4, (name, d.max())
+
+
 @pytest.mark.parametrize("what,scale", [("dy", 1e-25), ("v", 1e-25), ("dy", 1e-34), ("dy", 1e25), ("v", 1e30)])
 @pytest.mark.parametrize("kind,n,m", [("backward", 300, 32), ("backward", 1500, 16), ("star", 300, 32),
                                       ("expectation", 300, 8)])
