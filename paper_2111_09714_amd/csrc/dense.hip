@@ -67,6 +67,13 @@ constexpr float kNearFloor = 1.0f / 64.0f;  // *YOSO: 1 - x^2 is raised to at le
 constexpr int kRowExp = 8;
 constexpr float kWeightMax = 32768.0f;
 
+// Counts: streamed rows up to which tiles have scales of their own beside their head's, as the
+// 16 x 16 form of these lengths has them.  (Where dY of half the rows lies 10^7 below the other
+// half's and keys share buckets within a half, m = 2, tau = 8, 900 rows: dK's median row 7e-4 off, with
+// scales per tile 7e-7.  The scan with a maximum per tile costs the backward of 384 x 512 1.8%, 1 x 512
+// 3%, 192 x 1000 forward 1 to 2%; longer sides nothing beyond 1%.)
+constexpr int kFineRows = 1024, kTileRows = 32, kFineTiles = kFineRows / kTileRows;
+
 struct TileSide {
     const void *fx, *fa;         // fixed side: cosine (or x) rows, rows of G
     const void *sx, *sg, *sy;    // streamed side: cosine rows, rows of G, rows summed
@@ -76,6 +83,7 @@ struct TileSide {
     float *part_p, *part_g;      // split > 1: their fp32 partial sums [split][bh][n_f][64]
     // partial maxima of |sg|, |sy| ([kMaxParts][64] per head, heads 4 kMaxParts 64 apart), or null: scanned
     const float *max_g, *max_y;
+    const float *tmax_g, *tmax_y;  // beside them: of each kTileRows-row tile ([kFineTiles] per head), n_s <= kFineRows
     int n_f, n_s;
 };
 
@@ -118,7 +126,9 @@ __device__ __forceinline__ void put_octet(float *row, int oct, const float v[8])
 // its traffic alone about 3).
 // Blocks past the planes' (`plane_blocks`) take partial maxima instead: block (b*4 + t)
 // kMaxParts + p writes the largest |x| of each of the 64 dims over the p-th of kMaxParts row ranges
-// of tensor t (0 Q, 1 dY, 2 K, 3 V) of head b, from which the tiles derive their scales.
+// of tensor t (0 Q, 1 dY, 2 K, 3 V) of head b, from which the tiles derive their scales.  Up to
+// kFineRows rows the ranges are whole tiles of kTileRows rows, whose largest |x| of all dims follows
+// ([4 b + t][kFineTiles] after the parts of all heads).
 template <int NW, bool BF16>
 __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restrict__ qcodes,
                                                         const uint16_t *__restrict__ kcodes,
@@ -131,12 +141,18 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
     constexpr int PW = NW == 16 ? 2 : 1, PT = NW / PW;  // planes stored per word group
     if (blockIdx.x >= plane_blocks) {
         const int64_t blk = blockIdx.x - plane_blocks;
+        const int64_t max_words = (gridDim.x - plane_blocks) * D;
         const int p = static_cast<int>(blk % kMaxParts), t = static_cast<int>(blk / kMaxParts) & 3;
         const int64_t b = blk / (4 * kMaxParts);
         const void *src = t == 0 ? q : t == 1 ? dy : t == 2 ? k : v;
-        const int64_t n = t < 2 ? n_q : n_k, per = (n + kMaxParts - 1) / kMaxParts;
+        const int64_t n = t < 2 ? n_q : n_k;
+        const bool fine = n <= kFineRows;
+        int64_t per = (n + kMaxParts - 1) / kMaxParts;
+        if (fine) per = (per + kTileRows - 1) / kTileRows * kTileRows;
         const int64_t r0 = min(n, p * per), r1 = min(n, r0 + per);
         const int64_t base = (b * n + r0) * D, count = (r1 - r0) * D;
+        __shared__ __align__(16) float wred[4][D];
+        __shared__ float tred[4][4];
         float mx[8] = {};  // (a thread keeps to dims 8 (t mod 8) + [0, 8))
         for (int64_t e0 = static_cast<int64_t>(threadIdx.x) * 8; e0 < count; e0 += 256 * 8 * 4) {
             float x[4][8];
@@ -150,12 +166,29 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
 #pragma unroll
                 for (int i = 0; i < 8; i++) mx[i] = fmaxf(mx[i], fabsf(x[u][i]));
         }
-        __shared__ __align__(16) float wred[4][D];
+        if (fine) {
+            // (at most 128 rows; the block takes 32 at a time)
+            static_assert(kFineRows <= kMaxParts * 128 && kTileRows == 32, "a range is four tiles at most");
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int64_t e = (static_cast<int64_t>(threadIdx.x) + u * 256) * 8;
+                float x[8] = {}, w = 0.f;
+                if (e < count) load8<BF16>(src, base + e, x);
+#pragma unroll
+                for (int i = 0; i < 8; i++) w = fmaxf(w, fabsf(x[i]));
+                w = wave_max(w);
+                if ((threadIdx.x & 63) == 0) tred[u][threadIdx.x >> 6] = w;
+            }
+        }
         octet_max(mx);
         if ((threadIdx.x & 63) < 8) put_octet(wred[threadIdx.x >> 6], threadIdx.x & 7, mx);
         __syncthreads();
         const int d = threadIdx.x;
         if (d < D) pmax[blk * D + d] = fmaxf(fmaxf(wred[0][d], wred[1][d]), fmaxf(wred[2][d], wred[3][d]));
+        const int64_t tile = r0 / kTileRows + d;
+        if (fine && d < 4 && tile * kTileRows < r1)
+            pmax[max_words + (blk / kMaxParts) * kFineTiles + tile] =
+                fmaxf(fmaxf(tred[d][0], tred[d][1]), fmaxf(tred[d][2], tred[d][3]));
         return;
     }
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -364,6 +397,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr int kFE = kCountG ? kFixedExpCount : kFixedExp;
     // the rows that counts alone weight (dV's dY, the forward's V) are scaled dim by dim
     constexpr bool kDims = kP && !kX;
+    constexpr bool kFine = !kStar;  // tiles may have scales of their own
     constexpr bool kOwnPlanes = !kExp && !kG;  // the forward: planes built here from the codes
     constexpr int PW = NW == 16 ? 2 : 1;       // word groups of 32 hashes
     constexpr int T = 8 * WAVES;             // streamed rows per tile
@@ -379,12 +413,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr int OX0 = 0, OG = kExp ? 2 * TB : 0, OY = OG + (kG ? 2 * TB : 0), OX = kStar ? OY : OX0;
     constexpr int OC = OY + 2 * TB, OP = OC + 2 * CB;
     constexpr int OSUM = kP && kG ? OG : OY;  // the first rows that sums read
-    constexpr int OT = OY + 2 * TB;  // YOSO-E: a word per tile of each streamed tensor (sy, then sg)
+    // a word per tile of each streamed tensor, sy, then sg (counts: of up to kFineRows rows)
+    constexpr int OT = kExp ? OY + 2 * TB : OP + 2 * PB;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ float wmax[2][WAVES];
-    __shared__ int wfar[WAVES];  // YOSO-E: a tile far below its head
+    __shared__ int wfar[WAVES];  // a tile far below its head
     __shared__ __align__(16) float dmax[kDims ? WAVES : 1][D];  // the waves' maxima per dim
-    __shared__ __align__(16) float dscale[kDims ? D + 8 : 4];   // 2^(13 - e_d); eight zeros
+    __shared__ __align__(16) float dscale[kDims ? D : 4];       // 2^(13 - e_d)
     __shared__ __align__(16) int dexp[kDims ? D : 4];           // e_d: the dim's |values| are below 2^e_d
     const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bytes)smem));
 
@@ -435,9 +470,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // it, so that the scales, and the results, do not depend on the share)
     float mg = 0.f, my = 0.f, md[8] = {};
     const bool have_max = a.max_y != nullptr;
-    // YOSO-E: of each tile of T rows, too (words at OT); a wave takes 64 rows at a time
-    const int ntiles = kExp ? (ns + T - 1) / T : 0;
-    if constexpr (kExp) {
+    // of each tile of T rows, too (words at OT); a wave scans 64 rows at a time
+    const bool fine = kExp || (kFine && ns <= kFineRows);
+    const int ntiles = fine ? (ns + T - 1) / T : 0;
+    const int nwords = kExp ? ntiles : kFineTiles;
+    if (kFine && fine && !have_max) {
         for (int g0 = 64 * wave; g0 < ns; g0 += 64 * WAVES) {
             Raw<BF16> u[8], w[8];
 #pragma unroll
@@ -448,17 +485,31 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             }
 #pragma unroll
             for (int h = 0; h < 64 / T; h++) {
-                float ty = 0.f, tg = 0.f;
+                float ty = 0.f, tg = 0.f, td[8] = {};
 #pragma unroll
                 for (int i = h * (T / 8); i < (h + 1) * (T / 8); i++) {
                     float v[8];
                     raw_values<BF16>(u[i], v);
 #pragma unroll
-                    for (int e = 0; e < 8; e++) ty = fmaxf(ty, fabsf(v[e]));
+                    for (int e = 0; e < 8; e++) {
+                        if constexpr (kDims && !kG) td[e] = fmaxf(td[e], fabsf(v[e]));
+                        else ty = fmaxf(ty, fabsf(v[e]));
+                    }
                     if constexpr (kG) {
                         raw_values<BF16>(w[i], v);
 #pragma unroll
-                        for (int e = 0; e < 8; e++) tg = fmaxf(tg, fabsf(v[e]));
+                        for (int e = 0; e < 8; e++) {
+                            if constexpr (kDims) td[e] = fmaxf(td[e], fabsf(v[e]));
+                            else tg = fmaxf(tg, fabsf(v[e]));
+                        }
+                    }
+                }
+                if constexpr (kDims) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++) {
+                        md[e] = fmaxf(md[e], td[e]);
+                        if constexpr (kG) tg = fmaxf(tg, td[e]);
+                        else ty = fmaxf(ty, td[e]);
                     }
                 }
                 ty = wave_max(ty);
@@ -466,7 +517,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 const int tile = g0 / T + h;
                 if (lane == 0 && tile < ntiles) {
                     lds_put<float>(lds0 + OT + 4 * tile, ty);
-                    if constexpr (kG) lds_put<float>(lds0 + OT + 4 * (ntiles + tile), tg);
+                    if constexpr (kG) lds_put<float>(lds0 + OT + 4 * (nwords + tile), tg);
                 }
                 my = fmaxf(my, ty);
                 mg = fmaxf(mg, tg);
@@ -487,8 +538,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
             for (int i = 0; i < 8; i++) md[i] = src[e + i];
         }
+        if (kFine && tid < ntiles) {
+            auto tile_max = [&](const float *t, int to) {
+                const float *w = t + b * (4 * kFineTiles) + tid * (T / kTileRows);
+                float m = w[0];
+                if (T > kTileRows && tid * T + kTileRows < ns) m = fmaxf(m, w[1]);
+                lds_put<float>(lds0 + OT + 4 * to, m);
+            };
+            tile_max(a.tmax_y, tid);
+            if constexpr (kG) tile_max(a.tmax_g, nwords + tid);
+        }
     }
-    for (int c = have_max || kExp ? ns : srow; c < ns; c += 4 * T) {
+    for (int c = have_max || fine ? ns : srow; c < ns; c += 4 * T) {
         Raw<BF16> u[4], w[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -621,16 +682,19 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const int ey = __builtin_amdgcn_readfirstlane(scale_exp(hy));
     const int eg = kG ? __builtin_amdgcn_readfirstlane(scale_exp(hg)) : 0;
     const float scy = ldexpf(1.0f, 13 - ey), scg = ldexpf(1.0f, 13 - eg);
-    // YOSO-E: the exponents of the tiles.  A tile keeps its head's until its largest value is 2^8
-    // below (then it has 30 bits left above the pairs' end), and follows it down to 2^40.
+    // The exponents of the tiles.  A tile keeps its head's until its largest value is 2^8
+    // below (then it has 30 bits left above the pairs' end), and follows it down to 2^40.  (Counts:
+    // up to kFineRows rows.)
     bool varied = false;  // (no tile has: nothing of this in the loop)
-    if constexpr (kExp) {
+    if (kFine && ntiles > 0) {
         bool far = false;
         for (int i = tid; i < (kG ? 2 : 1) * ntiles; i += 64 * WAVES) {
-            const float m = lds_get<float>(lds0 + OT + 4 * i);
-            const int head = i < ntiles ? ey : eg, e = m > 0.f ? scale_exp(m) : head;
+            const bool y = i < ntiles;
+            const int at = lds0 + OT + 4 * (y ? i : nwords + i - ntiles);
+            const float m = lds_get<float>(at);
+            const int head = y ? ey : eg, e = m > 0.f ? scale_exp(m) : head;
             far = far || e < head - 8;
-            lds_put<int>(lds0 + OT + 4 * i, e < head - 8 ? max(e, head - 40) : head);
+            lds_put<int>(at, e < head - 8 ? max(e, head - 40) : head);
         }
         const bool any = __builtin_amdgcn_ballot_w64(far) != 0;
         if (lane == 0) wfar[wave] = any ? 1 : 0;
@@ -641,17 +705,43 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         varied = __builtin_amdgcn_readfirstlane(f) != 0;
     }
     auto tile_y = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (c0 / T)); };
-    auto tile_g = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (ntiles + c0 / T)); };
+    auto tile_g = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (nwords + c0 / T)); };
     if constexpr (kDims) {
-        if (tid < D + 8) {
+        if (tid < D) {
             float m = 0.f;
 #pragma unroll
-            for (int w = 0; w < WAVES; w++) m = fmaxf(m, dmax[w][tid & (D - 1)]);
+            for (int w = 0; w < WAVES; w++) m = fmaxf(m, dmax[w][tid]);
             const int e = m > 0.f ? scale_exp(m) : -100;  // (a dim of zeros: nothing of a)
-            dscale[tid] = tid < D ? ldexpf(1.0f, 13 - e) : 0.f;
-            if (tid < D) dexp[tid] = e;
+            dscale[tid] = ldexpf(1.0f, 13 - e);
+            dexp[tid] = e;
         }
         __syncthreads();
+        // A tile of rows scaled dim by dim follows the dim that lies least below its own of the head
+        if (varied) {
+            constexpr int to = OT + (kG ? 4 * kFineTiles : 0);
+            const int head = kG ? eg : ey;
+            for (int t = wave; t < ntiles; t += WAVES) {
+                if (lds_get<int>(lds0 + to + 4 * t) == head) continue;  // (its largest value is not far below)
+                float m[8] = {};
+                for (int i = 0; i < T / 8; i++) {
+                    const int64_t off = (b * ns + min(t * T + 8 * i + (lane >> 3), ns - 1)) * D + 8 * (lane & 7);
+                    Raw<BF16> u;
+                    raw_load<BF16>(u, kG ? a.sg : a.sy, off);
+                    float v[8];
+                    raw_values<BF16>(u, v);
+#pragma unroll
+                    for (int e = 0; e < 8; e++) m[e] = fmaxf(m[e], fabsf(v[e]));
+                }
+                octet_max(m);
+                float above = -40.f;
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    if (m[e] > 0.f) above = fmaxf(above, static_cast<float>(scale_exp(m[e]) - dexp[8 * (lane & 7) + e]));
+                const int d = static_cast<int>(wave_max(above + 64.f)) - 64;
+                if (lane == 0) lds_put<int>(lds0 + to + 4 * t, d < -8 ? head + d : head);
+            }
+            __syncthreads();
+        }
         // G = a . g: what scales a dim of g is taken back from a (up to the head's power)
         if constexpr (kG) {
 #pragma unroll
@@ -661,6 +751,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             fix_a();
         }
     }
+
+    // the scales of the tile that is staged (of rows scaled dim by dim: beside those)
+    float sty = kDims && !kG ? 1.0f : scy, stg = kDims ? 1.0f : scg;
+    auto stage_scales = [&](int c0) {
+        sty = ldexpf(1.0f, (kDims && !kG ? ey : 13) - __builtin_amdgcn_readfirstlane(tile_y(c0)));
+        if constexpr (kG) stg = ldexpf(1.0f, (kDims ? eg : 13) - __builtin_amdgcn_readfirstlane(tile_g(c0)));
+    };
 
     // convert and stage the tensor held in the raw registers (rows past cs1 as zeros)
     const uint32_t st_h = lane_base(lds0 + srow * 256 + ((soct ^ tswz(srow)) << 4));
@@ -685,19 +782,19 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         auto put_dims = [&](uint32_t t) {
             float v[8];
             raw_values<BF16>(raw, v);
-            const float *sc = dscale + (ok ? 8 * soct : D);
+            const float *sc = dscale + 8 * soct;
             const float4 s0 = reinterpret_cast<const float4 *>(sc)[0], s1 = reinterpret_cast<const float4 *>(sc)[1];
             v[0] *= s0.x; v[1] *= s0.y; v[2] *= s0.z; v[3] *= s0.w;
             v[4] *= s1.x; v[5] *= s1.y; v[6] *= s1.z; v[7] *= s1.w;
             half8 h, l;
-            split8_pk(v, 1.0f, h, l);
+            split8_pk(v, ok ? (kG ? stg : sty) : 0.f, h, l);
             lds_put<half8>(st_h + t, h);
             if (!BF16) lds_put<half8>(st_l + t, l);
         };
         if (kDims && !kG) put_dims(OY + bi * TB);
-        else if (part == 0) put(OY + bi * TB, raw, varied ? ldexpf(1.0f, 13 - tile_y(c0)) : scy, !BF16, false);
+        else if (part == 0) put(OY + bi * TB, raw, sty, !BF16, false);
         else if (kDims && part == 1) put_dims(OG + bi * TB);
-        else if (kG && part == 1) put(OG + bi * TB, raw, varied ? ldexpf(1.0f, 13 - tile_g(c0)) : scg, !BF16, false);
+        else if (kG && part == 1) put(OG + bi * TB, raw, stg, !BF16, false);
         else put(OX + bi * TB, raw, 1.0f, true, true);
     };
 
@@ -1156,7 +1253,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         };
         if (frow < nf) {
             if constexpr (kP) {
-                const int e1 = kDims ? 0 : kG ? cg : cy;
+                const int e1 = (kG ? cg : cy) - (kDims ? (kG ? eg : ey) : 0);
                 // (the dQ side of a launch for both sides has no P output)
                 if (a.out_p != nullptr)
                     put(a.out_p, a.part_p, outp, kExp ? args.pinv : 1.0f / static_cast<float>(args.m),
@@ -1178,6 +1275,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     const int clast = cs0 < cs1 ? cs0 + (cs1 - 1 - cs0) / T * T : cs0;
     if (cs0 < cs1) {
         load_planes(cs0);
+        if (kFine && varied) stage_scales(cs0);
 #pragma unroll
         for (int i = 0; i < kParts; i++) {
             if (i > 0) load_part(cs0, i);
@@ -1211,7 +1309,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         const int c1 = min(c0 + T, clast), c2n = min(c0 + 2 * T, clast), c3 = min(c0 + 3 * T, clast);
         Words w[2];
         load_words(w[0], nxt, 0);
-        if (kExp && __builtin_expect(varied, 0)) {
+        if (kFine && __builtin_expect(varied, 0)) {
             // the running sums in the tile's units
             const int ty = __builtin_amdgcn_readfirstlane(tile_y(c0));
             const int tg = kG ? __builtin_amdgcn_readfirstlane(tile_g(c0)) : 0;
@@ -1227,6 +1325,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 cy = ty;
                 cg = tg;
             }
+            stage_scales(c1);
         }
         compute(cur, [&](int i, int half) {
             if (half == 0) {
@@ -1338,8 +1437,10 @@ template <int WT, int SUM, bool BF16, int NW, int WAVES>
 hipError_t launch_tiles_w(const TileArgs &a, hipStream_t stream, const char *name) {
     const int64_t blocks = side_blocks(a, 32 * WAVES) * a.split;
     if (blocks == 0) return hipSuccess;
-    // (YOSO-E: a word per tile of each streamed tensor, at most 16 KiB)
-    const int words = WT == kWeightExpect ? (SUM == kSumP ? 1 : 2) * ((a.side[0].n_s + 8 * WAVES - 1) / (8 * WAVES)) : 0;
+    // a word per tile of each streamed tensor (YOSO-E: at most 16 KiB; counts: of kFineRows rows)
+    const int words = WT == kWeightStar ? 0
+                      : WT == kWeightExpect ? (SUM == kSumP ? 1 : 2) * ((a.side[0].n_s + 8 * WAVES - 1) / (8 * WAVES))
+                                            : (SUM == kSumP ? 1 : 2) * kFineTiles;
     KernelTimer timer(name, stream);
     hipLaunchKernelGGL((tile_kernel<WT, SUM, BF16, NW, WAVES>), dim3(static_cast<unsigned>(blocks)), dim3(64 * WAVES),
                        (tile_lds<WT, SUM, NW, WAVES>() + 4 * words), stream, a);
@@ -1465,18 +1566,19 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     if (e != hipSuccess) return e;
     const int64_t nq = rows_q * D, nk = rows_k * D;
     auto pmax = [&](int i) { return plan.maxima ? t.pmax + i * kMaxParts * D : nullptr; };
+    auto tmax = [&](int i) { return t.pmax + t.bh * 4 * kMaxParts * D + i * kFineTiles; };
     TileArgs a{};
     a.bh = t.bh; a.m = t.m; a.tau = t.tau;
     TileSide kv{}, q{};
     // keys fixed (a = V), queries streamed (g = dY, y = Q)
     kv.fa = t.v; kv.sg = t.dy; kv.sy = t.q; kv.fpl = t.kpl; kv.spl = t.qpl;
     kv.out_p = t.dv; kv.out_g = t.dk;
-    kv.max_g = pmax(1); kv.max_y = pmax(0);
+    kv.max_g = pmax(1); kv.max_y = pmax(0); kv.tmax_g = tmax(1); kv.tmax_y = tmax(0);
     kv.n_f = static_cast<int>(t.n_k); kv.n_s = static_cast<int>(t.n_q);
     // queries fixed (a = dY), keys streamed (g = V, y = K)
     q.fa = t.dy; q.sg = t.v; q.sy = t.k; q.fpl = t.qpl; q.spl = t.kpl;
     q.out_g = t.dq;
-    q.max_g = pmax(3); q.max_y = pmax(2);
+    q.max_g = pmax(3); q.max_y = pmax(2); q.tmax_g = tmax(3); q.tmax_y = tmax(2);
     q.n_f = static_cast<int>(t.n_q); q.n_s = static_cast<int>(t.n_k);
     q.part_g = t.part;
     kv.part_g = t.part + (plan.q.split > 1 ? plan.q.split * nq : 0);

@@ -93,7 +93,7 @@ struct TileBackward {
     int m, tau;
     bool star;
     uint32_t *qpl, *kpl;  // scratch: bit planes [bh][n][tile_plane_words]
-    float *pmax;          // scratch: partial maxima [bh][4][kMaxParts][64] of |Q|, |dY|, |K|, |V| per dim
+    float *pmax;          // scratch: partial maxima [bh][4][kMaxParts][64] of |Q|, |dY|, |K|, |V| per dim; of tiles [bh][4][32]
     float *part;          // scratch: fp32 partial outputs of launches that split the streamed rows
     size_t part_bytes;
 };

@@ -2339,7 +2339,7 @@ bool tile_star_form(int64_t bh, int64_t n_q, int64_t n_k, int m, int tau, bool b
 }
 
 // The dense tiles of dense.hip on this layout's scratch: the planes (at most 64 bytes per
-// row) take the space of the fp16 copies of Q and K (256 bytes), the maxima (8 KiB per head, only
+// row) take the space of the fp16 copies of Q and K (256 bytes), the maxima (8.5 KiB per head, only
 // where a side has 128 rows or more: 32 KiB) that of dY or V, partial outputs that of the
 // partial rows.
 hipError_t launch_tiles_on(const uint16_t *qcodes, const uint16_t *kcodes, const void *q, const void *k, const void *v,

@@ -189,6 +189,50 @@ def test_tiles_resolve_every_feature_dim(bh, nq, nk, m, tau, dtype):
     check_all(f"dims {bh}x{nq}x{nk} {dtype}", [("dq", host(dq[sl]), rq), ("dk", host(dk[sl]), rk)], TOL[dtype])
 
 
+@pytest.mark.parametrize("bh,nq,nk,m,tau,dtype", [
+    (1, 1024, 1000, 32, 8, "f32"),    # both sides in one launch, split; 32-row tiles
+    (1, 1024, 1000, 32, 8, "bf16"),
+    (1, 900, 4000, 16, 9, "f32"),     # one side of few rows, one of many
+    (64, 600, 1000, 48, 8, "f32"),    # a launch per side, scanned by each workgroup
+    (96, 1000, 1000, 32, 8, "f32"),   # 64-row tiles; the forward in tiles as well
+    (96, 1000, 1000, 32, 8, "bf16"),
+])
+@pytest.mark.parametrize("ratio", [1e-5, 1e-11])
+def test_rows_far_apart(bh, nq, nk, m, tau, dtype, ratio):
+    """Two opposite groups of rows that share no bucket, the first with dY, V, Q and K `ratio`
+    times the second's (codes do not depend on a row's length): up to 1024 streamed rows, a tile far below
+    its head has scales of its own, so the first group's outputs are as good as the second's."""
+    g = np.random.default_rng(9300 + nq + m)
+    unit = lambda a: a / np.linalg.norm(a, axis=-1, keepdims=True)
+    u = unit(g.standard_normal((bh, 1, 64)))
+    half = lambda n: n // 128 * 64
+    first = lambda n: (np.arange(n) < half(n))[None, :, None]
+    rows = lambda n: unit(np.where(first(n), 1.0, -1.0) * 3.0 * u + unit(g.standard_normal((bh, n, 64))))
+    size = lambda n: np.where(first(n), ratio, 1.0)
+    q, k = rows(nq) * size(nq), rows(nk) * size(nk)
+    v, dy = g.standard_normal((bh, nk, 64)) * size(nk), g.standard_normal((bh, nq, 64)) * size(nq)
+    q, k, v, dy = (to_dev(a, dtype) for a in (q, k, v, dy))
+    qc, kc = Y.hash_qk(q, k, torch.from_numpy(g.standard_normal((64, m * tau)).astype(np.float32)).cuda(), m, tau)
+    y, form = timed(("dense_fwd_kernel",), lambda: Y.forward(qc, kc, v, m, tau))
+    assert (form["dense_fwd_kernel"] == 1) == (bh > 1), form
+    (dq, dk, dv), ran = timed(FORMS, lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran["tile_kernel"] >= 1, ran
+    sl = [0, bh - 1] if bh > 1 else [0]
+    c = (codes_np(qc[sl]), codes_np(kc[sl]))
+    ry = oracle.forward(*c, host(v[sl]), m, tau)
+    rq, rk, rv = oracle.backward(*c, host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]), m, tau)
+    # (dQ of a query streams the keys, dK and dV of a key the queries)
+    outs = [("y", y, ry, nq, nk), ("dq", dq, rq, nq, nk), ("dk", dk, rk, nk, nq), ("dv", dv, rv, nk, nq)]
+    for name, got, ref, n, streamed in outs:
+        got = host(got[sl])
+        for part in (slice(0, half(n)), slice(half(n), n)):
+            if part.start == 0 and (streamed > 1024 or (name == "y" and form["dense_fwd_kernel"] == 0)):
+                continue  # (one scale per head or bucket table)
+            err = np.linalg.norm(got[:, part] - ref[:, part]) / np.linalg.norm(ref[:, part])
+            print(f"[far apart {bh}x{nq}x{nk} m{m} {dtype} {ratio:g}] {name} from row {part.start}: {err:.2e}")
+            assert err <= TOL[dtype], (name, part, err)
+
+
 @pytest.mark.parametrize("bh,nq,nk,tau", [(1, 300, 5, 8), (2, 333, 290, 8), (300, 300, 130, 8), (1, 1000, 1500, 9)])
 @pytest.mark.parametrize("ratio", [1e-7, 1e-4])
 def test_expectation_rows_far_apart(bh, nq, nk, tau, ratio):
