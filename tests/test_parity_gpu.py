@@ -86,15 +86,15 @@ SMALL = [
     (1, 200, 150, 32, 12, "bf16"),
     (2, 1, 1, 8, 4, "f32"),
     (1, 17, 33, 7, 2, "bf16"),
-    # many heads of short sequences: the bucket sort's one-wave blocks, the dense
-    # forward and the dense backward
+    # many heads of short sequences: the dense forms of the forward and the backward
     (40, 300, 257, 32, 8, "f32"),
     (32, 129, 1000, 33, 12, "bf16"),
-    # above 1024 rows on a side the pair passes serve dQ, dK (below, the dense form)
+    # above 1024 rows on a side the rule weighs the dense tiles against the pair passes (which form
+    # serves these is the library's choice; test_pairs_gpu.py holds the pairs' own cases)
     (1, 1025, 1100, 7, 5, "f32"),
     (2, 1500, 1030, 16, 8, "bf16"),
-    # the most hashes (m = 64) on the pair path: eight gather lanes per query in the
-    # tables, 64 partial rows per row in the hash sums
+    # the most hashes (m = 64): eight gather lanes per query in the tables, two plane words per
+    # bit in the dense tiles
     (1, 1100, 1500, 64, 8, "f32"),
     (1, 2000, 1100, 64, 7, "bf16"),
 ]
@@ -243,7 +243,8 @@ def large_bucket_share(qc, kc, tau, t=None):
 
 
 TABLE_FORM = [
-    # (bh, n_q, n_k, m, tau, dtype, dist): buckets of hundreds of rows on both sides
+    # (bh, n_q, n_k, m, tau, dtype, dist): buckets of hundreds of rows on both sides.  (The dense tiles
+    # serve all but the last; test_pairs_gpu.py holds the bucket form at such lengths.)
     (2, 1500, 1100, 4, 4, "f32", "gauss"),     # 16 buckets, every one large
     (1, 2000, 1300, 6, 6, "f32", "mixture"),   # large and small buckets side by side in one row tile
     (2, 1100, 3000, 3, 3, "bf16", "mixture"),
@@ -254,9 +255,9 @@ TABLE_FORM = [
 
 @pytest.mark.parametrize("bh,nq,nk,m,tau,dtype,dist", TABLE_FORM)
 def test_bucket_table_form(bh, nq, nk, m, tau, dtype, dist):
-    """Large buckets: their dQ, dK rows come from one 64 x 64 matrix per bucket
-    (the table form) while the other buckets keep the pair passes; every row is
-    checked against the oracle's pairwise sums."""
+    """Large buckets: where the pair passes serve the call, their dQ, dK rows come from one
+    64 x 64 matrix per bucket (the table form) while the other buckets keep the passes; every row
+    is checked against the oracle's pairwise sums."""
     g = run_case(bh, nq, nk, m, tau, dtype, dist)
     share = large_bucket_share(g["qc"], g["kc"], tau)
     log(f"[table form {bh}x{nq}x{nk} tau {tau} {dist}] rows in large buckets: {share:.3f}")
@@ -307,9 +308,9 @@ def test_backward_far_from_unit_scale(what, scale):
 
 @pytest.mark.parametrize("what,scale", [("dy", 1e-6), ("v", 1e3), ("rows", None)])
 def test_bucket_table_form_far_from_unit_scale(what, scale):
-    """The table form's per-bucket power-of-two scaling of M = sum a' b^T: small and
-    large gradients and rows of very different size (10^-4 .. 1 in dY, 10^-3 .. 10
-    in V) in buckets of a few hundred rows."""
+    """Small and large gradients and rows of very different size (10^-4 .. 1 in dY, 10^-3 .. 10
+    in V) in buckets of a few hundred rows.  (The dense tiles serve this length; test_pairs_gpu.py holds the
+    per-bucket power-of-two scaling of M = sum a' b^T.)"""
     bh, nq, nk, m, tau = 2, 1200, 1400, 6, 4
     name = f"table form scaled {what} {scale}"
     log(f"[{name}] start")

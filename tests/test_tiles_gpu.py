@@ -385,9 +385,11 @@ def test_forward_rule(bh, nq, nk, m, tau, dtype, form):
 ])
 def test_forward_tiles(bh, nq, nk, m, tau, dtype, kernel):
     (qc, kc), (q, k, v, dy) = inputs(bh, nq, nk, m, tau, dtype)
-    y, ran = timed(("dense_fwd_kernel", "table_kernel"), lambda: Y.forward(qc, kc, v, m, tau, n_q=nq))
+    names = ("dense_fwd_kernel", "tile_fwd_kernel", "table_kernel")
+    y, ran = timed(names, lambda: Y.forward(qc, kc, v, m, tau, n_q=nq))
+    assert ran["tile_fwd_kernel"] == (1 if kernel == "tile" else 0), ran
     if kernel == "tile":
-        assert ran == {"dense_fwd_kernel": 1, "table_kernel": 0}, ran
+        assert ran == {"dense_fwd_kernel": 1, "tile_fwd_kernel": 1, "table_kernel": 0}, ran
     assert torch.equal(y, Y.forward(qc, kc, v, m, tau, n_q=nq))
     sl = [0, bh - 1]
     ref = oracle.forward(codes_np(qc[sl]), codes_np(kc[sl]), host(v[sl]), m, tau)
