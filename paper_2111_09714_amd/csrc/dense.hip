@@ -69,8 +69,8 @@ constexpr float kWeightMax = 32768.0f;
 
 // Counts: streamed rows up to which tiles have scales of their own beside their head's, as the
 // 16 x 16 form of these lengths has them.  (Where dY of half the rows lies 10^7 below the other
-// half's and keys share buckets within a half, m = 2, tau = 8, 900 rows: dK's median row 7e-4 off, with
-// scales per tile 7e-7.  The scan with a maximum per tile costs the backward of 384 x 512 1.8%, 1 x 512
+// half's, m = 2, tau = 8, 900 rows: one row of dK in a hundred was 1.3e-3 or more off, now 7e-7.
+// The scan with a maximum per tile costs the backward of 384 x 512 1.8%, 1 x 512
 // 3%, 192 x 1000 forward 1 to 2%; longer sides nothing beyond 1%.)
 constexpr int kFineRows = 1024, kTileRows = 32, kFineTiles = kFineRows / kTileRows;
 
@@ -952,7 +952,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     // then added to the running ones: an MFMA rounds its sum every 4 rows and there are three
     // per product, and that many roundings of the large sums cost precision (dQ at 4096
     // rows: error 6.0e-7 summed directly).  (YOSO-E's dK and dV have no registers for it; their
-    // error is P's.)
+    // error is P's.  The backward's dV is summed directly too: its counts are exact, two products
+    // per step at most.)
     constexpr bool kTwoLevel = !BF16 && !(kExp && kP && kG);
 
     // *YOSO: the lane's fixed row takes its weights times 2^-kw (fp32: of one block times 1 / unscale)
@@ -1584,9 +1585,9 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     kv.part_g = t.part + (plan.q.split > 1 ? plan.q.split * nq : 0);
     kv.part_p = kv.part_g + plan.kv.split * nk;
     if (t.star) {
-        // *YOSO: both sides the same kernel; x = q . k of the rows as given
-        kv.fx = t.k; kv.sx = t.q; kv.out_p = nullptr;
-        q.fx = t.q; q.sx = t.k;
+        // *YOSO: both sides the same kernel; x = q . k of the rows as given, streamed as sy
+        kv.fx = t.k; kv.out_p = nullptr;
+        q.fx = t.q;
         a.side[0] = q; a.side[1] = kv; a.sides = 2; a.split = plan.kv.split;
         e = launch_tiles<kWeightStar, kSumG, BF16, NW>(a, plan.kv.wide, stream, "tile_star_kernel");
     } else if (plan.merged) {
