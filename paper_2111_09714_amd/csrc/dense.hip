@@ -91,6 +91,7 @@ struct TileArgs {
     TileSide side[2];
     int64_t bh;
     int sides, m, tau;
+    int parts;  // row ranges that have maxima (of the kMaxParts of a head), where there are any
     int split;  // workgroups per block of fixed rows, each streaming a contiguous share
     float pbase, pinv;  // YOSO-E: p = (base pbase)^tau, 1 / pbase^tau
 };
@@ -125,7 +126,7 @@ __device__ __forceinline__ void put_octet(float *row, int oct, const float v[8])
 // are read once; 2 operations per code and bit (4 us at 2 x 131072 rows of 32 8-bit codes,
 // its traffic alone about 3).
 // Blocks past the planes' (`plane_blocks`) take partial maxima instead: block (b*4 + t)
-// kMaxParts + p writes the largest |x| of each of the 64 dims over the p-th of kMaxParts row ranges
+// parts + p writes the largest |x| of each of the 64 dims over the p-th of `parts` row ranges
 // of tensor t (0 Q, 1 dY, 2 K, 3 V) of head b, from which the tiles derive their scales.  Up to
 // kFineRows rows the ranges are whole tiles of kTileRows rows, whose largest |x| of all dims follows
 // ([4 b + t][kFineTiles] after the parts of all heads).
@@ -137,23 +138,30 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
                                                         int64_t plane_blocks, const void *__restrict__ q,
                                                         const void *__restrict__ dy, const void *__restrict__ k,
                                                         const void *__restrict__ v, int64_t n_q, int64_t n_k,
-                                                        float *__restrict__ pmax) {
+                                                        float *__restrict__ pmax, int parts) {
     constexpr int PW = NW == 16 ? 2 : 1, PT = NW / PW;  // planes stored per word group
     if (blockIdx.x >= plane_blocks) {
-        const int64_t blk = blockIdx.x - plane_blocks;
-        const int64_t max_words = (gridDim.x - plane_blocks) * D;
-        const int p = static_cast<int>(blk % kMaxParts), t = static_cast<int>(blk / kMaxParts) & 3;
-        const int64_t b = blk / (4 * kMaxParts);
+        const int64_t blk = blockIdx.x - plane_blocks, bt = blk / parts;
+        const int p = static_cast<int>(blk - bt * parts), t = static_cast<int>(bt) & 3;
+        const int64_t b = bt >> 2, heads4 = (gridDim.x - plane_blocks) / parts;
+        float *dst = pmax + (bt * kMaxParts + p) * D;
         const void *src = t == 0 ? q : t == 1 ? dy : t == 2 ? k : v;
         const int64_t n = t < 2 ? n_q : n_k;
+        // (up to kFineRows rows: four tiles of 32 per block, one step of the block each)
+        static_assert(kFineRows == kMaxParts * 4 * kTileRows && kTileRows == 32, "");
         const bool fine = n <= kFineRows;
-        int64_t per = (n + kMaxParts - 1) / kMaxParts;
-        if (fine) per = (per + kTileRows - 1) / kTileRows * kTileRows;
+        const int64_t per = fine ? 4 * kTileRows : (n + kMaxParts - 1) / kMaxParts;
         const int64_t r0 = min(n, p * per), r1 = min(n, r0 + per);
+        const int d = threadIdx.x;
+        if (r0 == r1) {
+            if (d < D) dst[d] = 0.f;
+            return;
+        }
         const int64_t base = (b * n + r0) * D, count = (r1 - r0) * D;
         __shared__ __align__(16) float wred[4][D];
         __shared__ float tred[4][4];
-        float mx[8] = {};  // (a thread keeps to dims 8 (t mod 8) + [0, 8))
+        float mx[8] = {};   // (a thread keeps to dims 8 (t mod 8) + [0, 8))
+        float tmx[4] = {};  // its rows of the four tiles
         for (int64_t e0 = static_cast<int64_t>(threadIdx.x) * 8; e0 < count; e0 += 256 * 8 * 4) {
             float x[4][8];
 #pragma unroll
@@ -162,32 +170,30 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
                 load8<BF16>(src, base + (e < count ? e : e0), x[u]);  // (past the end: this thread's first again)
             }
 #pragma unroll
-            for (int u = 0; u < 4; u++)
+            for (int u = 0; u < 4; u++) {
+                float w = 0.f;
 #pragma unroll
-                for (int i = 0; i < 8; i++) mx[i] = fmaxf(mx[i], fabsf(x[u][i]));
+                for (int i = 0; i < 8; i++) {
+                    mx[i] = fmaxf(mx[i], fabsf(x[u][i]));
+                    w = fmaxf(w, fabsf(x[u][i]));
+                }
+                if (fine) tmx[u] = e0 + u * 256 * 8 < count ? w : 0.f;
+            }
         }
         if (fine) {
-            // (at most 128 rows; the block takes 32 at a time)
-            static_assert(kFineRows <= kMaxParts * 128 && kTileRows == 32, "a range is four tiles at most");
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                const int64_t e = (static_cast<int64_t>(threadIdx.x) + u * 256) * 8;
-                float x[8] = {}, w = 0.f;
-                if (e < count) load8<BF16>(src, base + e, x);
-#pragma unroll
-                for (int i = 0; i < 8; i++) w = fmaxf(w, fabsf(x[i]));
-                w = wave_max(w);
+                const float w = wave_max(tmx[u]);
                 if ((threadIdx.x & 63) == 0) tred[u][threadIdx.x >> 6] = w;
             }
         }
         octet_max(mx);
         if ((threadIdx.x & 63) < 8) put_octet(wred[threadIdx.x >> 6], threadIdx.x & 7, mx);
         __syncthreads();
-        const int d = threadIdx.x;
-        if (d < D) pmax[blk * D + d] = fmaxf(fmaxf(wred[0][d], wred[1][d]), fmaxf(wred[2][d], wred[3][d]));
+        if (d < D) dst[d] = fmaxf(fmaxf(wred[0][d], wred[1][d]), fmaxf(wred[2][d], wred[3][d]));
         const int64_t tile = r0 / kTileRows + d;
         if (fine && d < 4 && tile * kTileRows < r1)
-            pmax[max_words + (blk / kMaxParts) * kFineTiles + tile] =
+            pmax[heads4 * (kMaxParts * D) + bt * kFineTiles + tile] =
                 fmaxf(fmaxf(tred[d][0], tred[d][1]), fmaxf(tred[d][2], tred[d][3]));
         return;
     }
@@ -525,15 +531,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         }
     }
     if (have_max) {
-        const int64_t e = b * (4 * kMaxParts * D) + 8 * lane;
+        // (lane: dims 8 (lane mod 8) + [0, 8) of part lane / 8; of the last where there are fewer)
+        static_assert(kMaxParts == 8, "a part per eight lanes");
+        const int64_t e = (b * 4 * kMaxParts + min(lane >> 3, args.parts - 1)) * D + 8 * (lane & 7);
 #pragma unroll
         for (int i = 0; i < 8; i++) {
             my = fmaxf(my, a.max_y[e + i]);
             if constexpr (kG) mg = fmaxf(mg, a.max_g[e + i]);
         }
         if constexpr (kDims) {
-            // (lane: dims 8 (lane mod 8) + [0, 8) of part lane / 8)
-            static_assert(kMaxParts == 8, "a part per eight lanes");
             const float *src = kG ? a.max_g : a.max_y;
 #pragma unroll
             for (int i = 0; i < 8; i++) md[i] = src[e + i];
@@ -698,14 +704,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         }
         const bool any = __builtin_amdgcn_ballot_w64(far) != 0;
         if (lane == 0) wfar[wave] = any ? 1 : 0;
-        __syncthreads();
-        int f = 0;
-#pragma unroll
-        for (int w = 0; w < WAVES; w++) f |= wfar[w];
-        varied = __builtin_amdgcn_readfirstlane(f) != 0;
     }
-    auto tile_y = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (c0 / T)); };
-    auto tile_g = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (nwords + c0 / T)); };
     if constexpr (kDims) {
         if (tid < D) {
             float m = 0.f;
@@ -715,7 +714,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             dscale[tid] = ldexpf(1.0f, 13 - e);
             dexp[tid] = e;
         }
-        __syncthreads();
+    }
+    if (kDims || (kFine && ntiles > 0)) __syncthreads();
+    if (kFine && ntiles > 0) {
+        int f = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) f |= wfar[w];
+        varied = __builtin_amdgcn_readfirstlane(f) != 0;
+    }
+    auto tile_y = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (c0 / T)); };
+    auto tile_g = [&](int c0) { return lds_get<int>(lds0 + OT + 4 * (nwords + c0 / T)); };
+    if constexpr (kDims) {
         // A tile of rows scaled dim by dim follows the dim that lies least below its own of the head
         if (varied) {
             constexpr int to = OT + (kG ? 4 * kFineTiles : 0);
@@ -1555,13 +1564,17 @@ template <bool BF16, int NW>
 hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     const TilePlan plan = tile_plan(t.bh, t.n_q, t.n_k, t.star, t.part_bytes);
     const int64_t rows_q = t.bh * t.n_q, rows_k = t.bh * t.n_k;
+    // (row ranges of a tensor's maxima, of 128 rows up to kFineRows: 174 x 255 x 112 with eight for any
+    // length 18.6 us, of which most are empty, with two 11.3)
+    const int64_t longer = t.n_q > t.n_k ? t.n_q : t.n_k;
+    const int parts = longer <= kFineRows ? static_cast<int>((longer + 127) / 128) : kMaxParts;
     {
         const int64_t plane_blocks = ((rows_q + rows_k) * (NW == 16 ? 2 : 1) + 255) / 256;
-        const int64_t max_blocks = plan.maxima ? t.bh * 4 * kMaxParts : 0;
+        const int64_t max_blocks = plan.maxima ? t.bh * 4 * parts : 0;
         KernelTimer timer("tile_prep_kernel", stream);
         hipLaunchKernelGGL((tile_prep_kernel<NW, BF16>), dim3(static_cast<unsigned>(plane_blocks + max_blocks)),
                            dim3(256), 0, stream, t.qcodes, t.kcodes, t.qpl, t.kpl, rows_q, rows_k, t.m, t.tau,
-                           plane_blocks, t.q, t.dy, t.k, t.v, t.n_q, t.n_k, t.pmax);
+                           plane_blocks, t.q, t.dy, t.k, t.v, t.n_q, t.n_k, t.pmax, parts);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1569,7 +1582,7 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     auto pmax = [&](int i) { return plan.maxima ? t.pmax + i * kMaxParts * D : nullptr; };
     auto tmax = [&](int i) { return t.pmax + t.bh * 4 * kMaxParts * D + i * kFineTiles; };
     TileArgs a{};
-    a.bh = t.bh; a.m = t.m; a.tau = t.tau;
+    a.bh = t.bh; a.m = t.m; a.tau = t.tau; a.parts = parts;
     TileSide kv{}, q{};
     // keys fixed (a = V), queries streamed (g = dY, y = Q)
     kv.fa = t.v; kv.sg = t.dy; kv.sy = t.q; kv.fpl = t.kpl; kv.spl = t.qpl;
