@@ -29,12 +29,14 @@
 // which are normalised, keep both).  Scales, all powers of two but the first:
 //   cosine rows     unit length times 2^4
 //   fixed rows a    each row by 2^(6 - e), ||a|| < 2^e (counts: 2^(9 - e) and less)
-//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan;
-//                   YOSO-E: a tile of 32 or 64 rows far below its head by its own e);
-//                   those that counts alone weight (dV's dY, the forward's V) dim by dim, as
-//                   the bucket tables do, with the dims' powers taken back from a
-//   weights         |G| < 2^22, times C (or N, P) and a constant that keeps W below 2^15;
-//                   P itself by pbase^tau, just below 2^16 (expect_scale)
+//   streamed rows   each head's tensor by 2^(13 - e), max |x| < 2^e (found by a first scan); a
+//                   tile of 32 or 64 rows far below its head by its own e (YOSO-E; counts up
+//                   to kFineRows rows); those that counts alone weight (dV's dY, the
+//                   forward's V) dim by dim, as the bucket tables do, with the dims' powers
+//                   taken back from a
+//   weights         counts: |G| < 2^25 times C 2^-11, a row that meets a count of 4 or more scaled
+//                   down (widen); *YOSO: |G| < 2^22, each row to what comes (row_scale);
+//                   P by pbase^tau, just below 2^16 (expect_scale), G P by 2^-7 more
 #include <type_traits>
 
 #include "common.h"
