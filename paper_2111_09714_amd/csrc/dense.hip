@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
                                                         int64_t plane_blocks, const void *__restrict__ q,
                                                         const void *__restrict__ dy, const void *__restrict__ k,
                                                         const void *__restrict__ v, int64_t n_q, int64_t n_k,
-                                                        float *__restrict__ pmax, int parts) {
+                                                        float *__restrict__ pmax, int parts, int fine_per) {
     constexpr int PW = NW == 16 ? 2 : 1, PT = NW / PW;  // planes stored per word group
     if (blockIdx.x >= plane_blocks) {
         const int64_t blk = blockIdx.x - plane_blocks, bt = blk / parts;
@@ -149,10 +149,10 @@ __global__ __launch_bounds__(256) void tile_prep_kernel(const uint16_t *__restri
         float *dst = pmax + (bt * kMaxParts + p) * D;
         const void *src = t == 0 ? q : t == 1 ? dy : t == 2 ? k : v;
         const int64_t n = t < 2 ? n_q : n_k;
-        // (up to kFineRows rows: four tiles of 32 per block, one step of the block each)
+        // (up to kFineRows rows: `fine_per` per block, one to four tiles of 32, each one step of the block)
         static_assert(kFineRows == kMaxParts * 4 * kTileRows && kTileRows == 32, "");
         const bool fine = n <= kFineRows;
-        const int64_t per = fine ? 4 * kTileRows : (n + kMaxParts - 1) / kMaxParts;
+        const int64_t per = fine ? fine_per : (n + kMaxParts - 1) / kMaxParts;
         const int64_t r0 = min(n, p * per), r1 = min(n, r0 + per);
         const int d = threadIdx.x;
         if (r0 == r1) {
@@ -1566,17 +1566,21 @@ template <bool BF16, int NW>
 hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     const TilePlan plan = tile_plan(t.bh, t.n_q, t.n_k, t.star, t.part_bytes);
     const int64_t rows_q = t.bh * t.n_q, rows_k = t.bh * t.n_k;
-    // (row ranges of a tensor's maxima, of 128 rows up to kFineRows: 174 x 255 x 112 with eight for any
-    // length 18.6 us, of which most are empty, with two 11.3)
+    // Row ranges of a tensor's maxima.  Up to kFineRows rows: only those there are, of 128 rows where
+    // the heads alone fill the card (174 x 255 x 112, bf16: 18.6 us with eight ranges, most of them
+    // empty, 11.3 with two), else an eighth of the longer side in whole tiles (1 x 512: 4.8 us, with ranges of 128 5.4).
     const int64_t longer = t.n_q > t.n_k ? t.n_q : t.n_k;
-    const int parts = longer <= kFineRows ? static_cast<int>((longer + 127) / 128) : kMaxParts;
+    const int fine_per = longer > kFineRows || t.bh > 32
+                             ? kFineRows / kMaxParts
+                             : static_cast<int>((longer + kMaxParts * kTileRows - 1) / (kMaxParts * kTileRows)) * kTileRows;
+    const int parts = longer > kFineRows ? kMaxParts : static_cast<int>((longer + fine_per - 1) / fine_per);
     {
         const int64_t plane_blocks = ((rows_q + rows_k) * (NW == 16 ? 2 : 1) + 255) / 256;
         const int64_t max_blocks = plan.maxima ? t.bh * 4 * parts : 0;
         KernelTimer timer("tile_prep_kernel", stream);
         hipLaunchKernelGGL((tile_prep_kernel<NW, BF16>), dim3(static_cast<unsigned>(plane_blocks + max_blocks)),
                            dim3(256), 0, stream, t.qcodes, t.kcodes, t.qpl, t.kpl, rows_q, rows_k, t.m, t.tau,
-                           plane_blocks, t.q, t.dy, t.k, t.v, t.n_q, t.n_k, t.pmax, parts);
+                           plane_blocks, t.q, t.dy, t.k, t.v, t.n_q, t.n_k, t.pmax, parts, fine_per);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
