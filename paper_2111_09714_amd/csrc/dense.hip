@@ -1568,7 +1568,8 @@ hipError_t launch_tile_backward(const TileBackward &t, hipStream_t stream) {
     const int64_t rows_q = t.bh * t.n_q, rows_k = t.bh * t.n_k;
     // Row ranges of a tensor's maxima.  Up to kFineRows rows: only those there are, of 128 rows where
     // the heads alone fill the card (174 x 255 x 112, bf16: 18.6 us with eight ranges, most of them
-    // empty, 11.3 with two), else an eighth of the longer side in whole tiles (1 x 512: 4.8 us, with ranges of 128 5.4).
+    // empty, 11.3 with two), else an eighth of the longer side in whole tiles
+    // (1 x 512: 4.8 us, with ranges of 128 5.4).
     const int64_t longer = t.n_q > t.n_k ? t.n_q : t.n_k;
     const int fine_per = longer > kFineRows || t.bh > 32
                              ? kFineRows / kMaxParts
