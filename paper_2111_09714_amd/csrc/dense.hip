@@ -76,6 +76,16 @@ constexpr float kWeightMax = 32768.0f;
 // 3%, 192 x 1000 forward 1 to 2%; longer sides nothing beyond 1%.)
 constexpr int kFineRows = 1024, kTileRows = 32, kFineTiles = kFineRows / kTileRows;
 
+// Counts, fp32: streamed rows after which the running sums go to the output (or partial output), to
+// start again from zero.  A sum over 4096 rows is 128 additions to a running one, and where the
+// addends have one sign (clustered rows) their rounding, sqrt(128 / 3) times 0.29 of the last
+// place, is most of the error: dQ of 32 x 4096 clustered 2.71e-7, in parts of 2048 rows 2.30e-7 (the
+// pair passes 2.49e-7); m = 64 2.76e-7, in parts of 1024 2.15e-7 (2.32e-7).  Backward of 32 x 4096 1.06 ->
+// 1.09 ms, m = 48, whose registers spill more with it, 1.61 -> 1.76.  (dK and dV of twelve plane words
+// spill 50 more and are no less precise than the pairs: 2.60e-7 and 2.65e-7.)
+template <int NW>
+constexpr int kFlushRows = NW == 16 ? 1024 : 2048;
+
 struct TileSide {
     const void *fx, *fa;         // fixed side: cosine (or x) rows, rows of G
     const void *sx, *sg, *sy;    // streamed side: cosine rows, rows of G, rows summed
@@ -402,6 +412,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     constexpr bool kX = WT != kWeightCount;  // a scalar product x beside G
     constexpr bool kRowScale = kStar;        // weights scaled per fixed row as they come
     constexpr bool kCountG = kG && !kX;      // G weighted by counts
+    constexpr bool kFlush = kCountG && !BF16 && (NW != 12 || !kP);  // long sums in parts of kFlushRows rows
     constexpr int kFE = kCountG ? kFixedExpCount : kFixedExp;
     // the rows that counts alone weight (dV's dY, the forward's V) are scaled dim by dim
     constexpr bool kDims = kP && !kX;
@@ -1236,7 +1247,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
     int cy = ey, cg = eg;  // the exponents that the running sums are in
 
     // ---- outputs
-    auto finish = [&]() {
+    // (`again`: added to what a flush of the same sums has put there)
+    auto finish = [&](bool again) {
+        int row = tid;  // (frow again, not kept through the loop)
+        if constexpr (kFlush) asm volatile("" : "+v"(row));
+        const int h4 = (row >> 3) & 4;
+        row = r0 + 32 * (row >> 6) + (row & 31);
         // o c 2^e (the power apart: it may pass the range of a scale where the output does not)
         auto put = [&](void *dst, float *part, const floatx16 o[2], float c, int e0, bool dims) {
 #pragma unroll
@@ -1244,17 +1260,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     // lane (l31, hh) holds out[row l31][32 db + 8 u + 4 hh + (0..3)] in registers 4u .. 4u+3
-                    const int64_t off = (b * nf + frow) * D + 32 * db + 8 * u + 4 * hh;
+                    const int64_t off = (b * nf + row) * D + 32 * db + 8 * u + h4;
                     int4 e = make_int4(e0, e0, e0, e0);
                     if (dims) {
-                        const int4 ed = reinterpret_cast<const int4 *>(dexp)[8 * db + 2 * u + hh];
+                        const int4 ed = reinterpret_cast<const int4 *>(dexp)[8 * db + 2 * u + h4 / 4];
                         e = make_int4(e0 + ed.x, e0 + ed.y, e0 + ed.z, e0 + ed.w);
                     }
-                    const float4 x = make_float4(ldexpf(o[db][4 * u] * c, e.x), ldexpf(o[db][4 * u + 1] * c, e.y),
+                    float4 x = make_float4(ldexpf(o[db][4 * u] * c, e.x), ldexpf(o[db][4 * u + 1] * c, e.y),
                                                  ldexpf(o[db][4 * u + 2] * c, e.z), ldexpf(o[db][4 * u + 3] * c, e.w));
                     if (split > 1 || !BF16) {
-                        *reinterpret_cast<float4 *>(split > 1 ? part + sp * (args.bh * nf * D) + off
-                                                              : static_cast<float *>(dst) + off) = x;
+                        float4 *to = reinterpret_cast<float4 *>(split > 1 ? part + sp * (args.bh * nf * D) + off
+                                                                          : static_cast<float *>(dst) + off);
+                        if (kFlush && again) {
+                            const float4 y = *to;
+                            x = make_float4(y.x + x.x, y.y + x.y, y.z + x.z, y.w + x.w);
+                        }
+                        *to = x;
                     } else {
                         uint2 w;
                         w.x = static_cast<uint32_t>(f32_to_bf16(x.x)) | (static_cast<uint32_t>(f32_to_bf16(x.y)) << 16);
@@ -1263,7 +1284,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                     }
                 }
         };
-        if (frow < nf) {
+        if (row < nf) {
             if constexpr (kP) {
                 const int e1 = (kG ? cg : cy) - (kDims ? (kG ? eg : ey) : 0);
                 // (the dQ side of a launch for both sides has no P output)
@@ -1364,11 +1385,20 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         __syncthreads();
     };
     // (two steps per turn: the buffers' addresses are constants)
+    bool again = false;
     for (int c0 = cs0; c0 < cs1; c0 += 2 * T) {
         step(0, 1, c0);
         if (c0 + T < cs1) step(1, 0, c0 + T);
+        if (kFlush && __builtin_expect(((c0 + 2 * T - cs0) & (kFlushRows<NW> - 1)) == 0 && c0 + 2 * T < cs1, 0)) {
+            finish(again);
+            again = true;
+#pragma unroll
+            for (int db = 0; db < 2; db++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) outp[db][i] = outg[db][i] = 0.f;
+        }
     }
-    finish();
+    finish(again);
 }
 
 __global__ void zero_rows_kernel(uint32_t *__restrict__ p, int64_t words) {

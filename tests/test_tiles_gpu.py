@@ -233,6 +233,23 @@ def test_rows_far_apart(bh, nq, nk, m, tau, dtype, ratio):
             assert err <= TOL[dtype], (name, part, err)
 
 
+@pytest.mark.parametrize("m,bar", [(32, 2.5e-7), (48, 2.4e-7)])
+def test_long_sums_of_one_sign(m, bar):
+    """4096 clustered rows, not split: a running sum takes 128 additions of mostly one sign, each off by
+    0.29 of the last place (2^-23.5) or so, together sqrt(128 / 3) times that or 1.6e-7; in parts of 2048
+    rows 0.8e-7, beside 2.2e-7 of all else.  The bar is the error of the pair passes."""
+    bh, n, tau = 16, 4096, 8
+    (qc, kc), (q, k, v, dy) = inputs(bh, n, n, m, tau, "f32", "mixture")
+    (dq, dk, dv), ran = timed(FORMS, lambda: Y.backward(qc, kc, q, k, v, dy, m, tau))
+    assert ran["tile_kernel"] >= 1 and ran["dense_sum_kernel"] == 0, ran
+    sl = [0, bh - 1]
+    ref = oracle.backward(codes_np(qc[sl]), codes_np(kc[sl]), host(q[sl]), host(k[sl]), host(v[sl]), host(dy[sl]), m, tau)
+    for name, got, r in zip(("dq", "dk"), (dq, dk), ref):
+        err = np.linalg.norm(host(got[sl]) - r) / np.linalg.norm(r)
+        print(f"[long sums m{m}] {name}: {err:.3e}")
+        assert err <= bar, (name, err)
+
+
 @pytest.mark.parametrize("bh,nq,nk,tau", [(1, 300, 5, 8), (2, 333, 290, 8), (300, 300, 130, 8), (1, 1000, 1500, 9)])
 @pytest.mark.parametrize("ratio", [1e-7, 1e-4])
 def test_expectation_rows_far_apart(bh, nq, nk, tau, ratio):
