@@ -36,20 +36,25 @@
  *     magnitude; R is staged unscaled, so |R| must stay below 65504 (entries
  *     below about 2^-3 keep their value to 2^-24 absolute).  The backward and
  *     YOSO-E scale every operand by a power of two before it is split into
- *     fp16 (hi, lo) pairs (per head and tensor, or per row),
- *     so V, dY, Q, K may have any magnitude between about 2^-40 and 2^40;
- *     values more than about 2^20 below the largest of their head
- *     keep less than 22 significant bits.
+ *     fp16 (hi, lo) pairs, so V, dY, Q, K may have any magnitude between about
+ *     2^-40 and 2^40 (in the dense tiles any finite one, as far as the outputs have
+ *     a value).  The scale is that of the row, of its 32 or 64 row tile (YOSO-E, and
+ *     the backward of sides of up to 1024 rows) or of its head (longer sides); in
+ *     Y and dV from the dense tiles of each dim, too.  Values more than about 2^20 below the
+ *     largest that shares their scale keep less than 22 significant bits.
  *   - Precision.  Y and dV from the bucket tables are accumulated as exact fixed-point integers: each
  *     value of feature dim d is rounded to a multiple of 2^-k_d, where 2^k_d is
  *     the largest power of two keeping 2^k_d (1 + 2^-10) times a bound on every
  *     bucket sum of |value| of that dim below 2^30: the dim's sum of |value|
  *     over the n_src source rows, or, for fp32 outputs with n_src > 8192, the
  *     smaller of that sum and the largest bucket's row count times the dim's
- *     largest |value|; everything after that rounding is exact.  dQ and dK use fp32 accumulation of products formed
+ *     largest |value|; everything after that rounding is exact.  In the dense forms Y and dV
+ *     are fp32 sums of exact counts times pairs.  dQ and dK use fp32 accumulation of products formed
  *     from fp16 (hi, lo) pairs (about 22 significant bits; bf16 inputs are
- *     exact as the hi halves alone wherever they lie within 2^27 of their head's
- *     largest value); the contribution of each hash to a row is kept in 24-bit
+ *     exact as the hi halves alone wherever they lie within 2^27 of the largest
+ *     value of their scale).  The weights of pairs are held as such pairs as well, scaled so that one
+ *     hash's weight (YOSO-E: P = 1) lies near the top of fp16's range: weights more than 2^15 below
+ *     it, or in *YOSO below the largest of their row, keep less than 22 bits.  In the pair passes the contribution of each hash to a row is kept in 24-bit
  *     fixed point (one power-of-two exponent per row, exact to 2^-22 of that
  *     row's largest value; 16-bit, exact to 2^-15, for bf16 outputs, whose own
  *     rounding is 2^-9, four values of each row keeping 14 bits, 2^-13, beside
